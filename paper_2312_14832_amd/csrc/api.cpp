@@ -43,6 +43,7 @@ int slices_for(int64_t bytes, int64_t slice_bytes)
 // with the chunk slots of each.
 struct HostSliced {
     int S = 1, rows = 0, cols = 0, nb = kStreamNB, rb = kStreamRB;
+    int split = 0;   // the row sums are split by entries (Sliced::split)
     std::vector<int> rp, ci, src, brow, boff;
     std::vector<unsigned short> ro;   // per slice and row: start relative to its row block's first entry
     std::vector<int4> blk;   // per row block: first row, end row, first entry, end entry
@@ -72,12 +73,21 @@ void run_threads(int T, F &&fn)
         if (e) std::rethrow_exception(e);
 }
 
+// Row blocks from which a product's short-row sums are split by entries by
+// default: below that the partial pass is a few workgroups whose time is
+// latency, which the split's two extra barriers lengthen (the 5,000-entry LP:
+// 51k against 44k iterations per second in launched slots), while above it
+// the split evens out the threads' work (the 2e7-entry power-law LP: K' pass
+// 128 against 124 us).
+constexpr size_t kSplitMinBlocks = 1024;
+
 // Rows of the source CSR must have their columns sorted, so that each
 // slice's part of a row is one contiguous run.  The split and the row blocks
 // run on host threads (by row chunks, then by slices); the result does not
-// depend on the thread count.
+// depend on the thread count.  split (lp_options.split_sums): 1 or 0 as asked;
+// -1 splits a product of at least kSplitMinBlocks row blocks.
 void build_sliced(HostSliced &H, int rows, int cols, const std::vector<int> &rp, const std::vector<int> &ci, int S,
-                  int nb = kStreamNB, int rb = kStreamRB)
+                  int split, int nb = kStreamNB, int rb = kStreamRB)
 {
     if (nb > kStreamNB || nb < 1) nb = kStreamNB;   // a chunk is at most one staged block
     if (rb > kStreamRB || rb < 1) rb = kStreamRB;
@@ -158,36 +168,50 @@ void build_sliced(HostSliced &H, int rows, int cols, const std::vector<int> &rp,
         H.loff.push_back(next);
     }
 
-    // row blocks, slice by slice
+    // Row blocks, slice by slice.  Where rows of more than kWaveRow entries are
+    // scattered among short ones, they cut the runs of short rows to a few
+    // entries each (the power-law LP of 1e6 columns in one FP32 slice: 70
+    // entries to a K' block, and the pass took 289 us where K's, of the same
+    // nonzeros, took 58).  The split row sums need no such cut up to kMixRow,
+    // so a split product keeps those rows in the runs: 60 us.
     std::vector<std::vector<int4>> bs((size_t)S);
     const int T2 = std::max(1, std::min(host_threads(), S));
-    run_threads(T2, [&](int t) {
-        std::vector<int> brow;
-        std::vector<char> wave;
-        for (int sl = t; sl < S; sl += T2) {
-            const int *r = &H.rp[(size_t)sl * (rows + 1)];
-            std::vector<int4> &out = bs[(size_t)sl];
-            auto plain = [&](int r_begin, int r_end) {
-                brow.assign(1, r_begin);
-                wave.clear();
-                row_blocks(r, r_begin, r_end, brow, wave, nb, rb);
-                for (size_t k = 0; k + 1 < brow.size(); ++k) {
-                    const int r0 = brow[k], r1 = brow[k + 1];
-                    out.push_back(make_int4(r0, wave[k] ? ~r1 : r1, r[r0], r[r1]));
+    auto cut = [&](int short_max) {
+        run_threads(T2, [&](int t) {
+            std::vector<int> brow;
+            std::vector<char> wave;
+            for (int sl = t; sl < S; sl += T2) {
+                const int *r = &H.rp[(size_t)sl * (rows + 1)];
+                std::vector<int4> &out = bs[(size_t)sl];
+                out.clear();
+                auto plain = [&](int r_begin, int r_end) {
+                    brow.assign(1, r_begin);
+                    wave.clear();
+                    row_blocks(r, r_begin, r_end, brow, wave, nb, rb, short_max);
+                    for (size_t k = 0; k + 1 < brow.size(); ++k) {
+                        const int r0 = brow[k], r1 = brow[k + 1];
+                        out.push_back(make_int4(r0, wave[k] ? ~r1 : r1, r[r0], r[r1]));
+                    }
+                };
+                int start = 0;
+                for (size_t k = 0; k < H.lrow.size(); ++k) {
+                    const int lr = H.lrow[k];
+                    plain(start, lr);
+                    int slot = lslot[k * S + sl];
+                    for (int b = r[lr]; b < r[lr + 1]; b += nb)
+                        out.push_back(make_int4(~slot++, 0, b, std::min(b + nb, r[lr + 1])));
+                    start = lr + 1;
                 }
-            };
-            int start = 0;
-            for (size_t k = 0; k < H.lrow.size(); ++k) {
-                const int lr = H.lrow[k];
-                plain(start, lr);
-                int slot = lslot[k * S + sl];
-                for (int b = r[lr]; b < r[lr + 1]; b += nb)
-                    out.push_back(make_int4(~slot++, 0, b, std::min(b + nb, r[lr + 1])));
-                start = lr + 1;
+                plain(start, rows);
             }
-            plain(start, rows);
-        }
-    });
+        });
+        size_t n = 0;
+        for (const auto &b : bs) n += b.size();
+        return n;
+    };
+    const size_t apart = split == 1 ? 0 : cut(kWaveRow);
+    H.split = split == -1 ? apart >= kSplitMinBlocks : split;
+    if (H.split) cut(kMixRow);
     // row starts relative to their block (a block holds at most kStreamNB
     // entries unless it is a single row, so the offsets fit 16 bits)
     H.ro.assign((size_t)S * (size_t)rows, 0);
@@ -349,12 +373,12 @@ void sync(lp_problem *P) { HIPT(hipStreamSynchronize(P->stream)); }
 // Device side of a sliced product: structure uploaded from H, values gathered
 // from the scaled FP64 CSR values by the recorded source positions.
 template <typename T>
-Sliced<T> upload_sliced(lp_problem *P, const HostSliced &H, const double *scaled_csr_vals, int split)
+Sliced<T> upload_sliced(lp_problem *P, const HostSliced &H, const double *scaled_csr_vals)
 {
     const int64_t nnz = H.rp[(size_t)H.S * (H.rows + 1) - 1];
     Sliced<T> q{};
     q.S = H.S;
-    q.split = split;
+    q.split = H.split;
     q.rows = H.rows;
     q.grid = partial_grid(H.S, H.max_blocks);
     int *rp = (int *)P->dalloc(sizeof(int) * H.rp.size());
@@ -412,14 +436,6 @@ float time_product(lp_problem *P, const Sliced<T> &q, T *in, T *out, int64_t in_
     return ev.ms() / reps;
 }
 
-// Row blocks from which a product's short-row sums are split by entries by
-// default: below that the partial pass is a few workgroups whose time is
-// latency, which the split's two extra barriers lengthen (the 5,000-entry LP:
-// 51k against 44k iterations per second in launched slots), while above it
-// the split evens out the threads' work (the 2e7-entry power-law LP: K' pass
-// 128 against 124 us).
-constexpr size_t kSplitMinBlocks = 1024;
-
 // A trial layout replaces the incumbent only when it is this much faster, so
 // that near-ties (timing noise) keep the earlier, default-side layout and
 // two processes rarely pick different layouts.
@@ -435,18 +451,17 @@ constexpr float kTuneMargin = 0.97f;
 // chosen layout (same device arrays) and keeps the faster.
 template <typename T>
 Sliced<T> tuned_sliced(lp_problem *P, const HostSliced &H0, const std::vector<int> &rp, const std::vector<int> &ci,
-                       const double *vals, T *in, T *out, int64_t in_len, std::vector<TuneTrial> &log, int *shape,
-                       int split)
+                       const double *vals, T *in, T *out, int64_t in_len, std::vector<TuneTrial> &log, int *shape)
 {
-    Sliced<T> best = upload_sliced<T>(P, H0, vals, split);
+    Sliced<T> best = upload_sliced<T>(P, H0, vals);
     float best_ms = time_product<T>(P, best, in, out, in_len);
     log.push_back({H0.S, H0.nb, H0.rb, best_ms});
     shape[0] = H0.S; shape[1] = H0.nb; shape[2] = H0.rb;
     // time one layout; keep it if it is the fastest so far
     auto trial = [&](int S, int nb, int rb) {
         HostSliced H;
-        build_sliced(H, H0.rows, H0.cols, rp, ci, S, nb, rb);
-        Sliced<T> q = upload_sliced<T>(P, H, vals, split);
+        build_sliced(H, H0.rows, H0.cols, rp, ci, S, H0.split, nb, rb);
+        Sliced<T> q = upload_sliced<T>(P, H, vals);
         const float ms = time_product<T>(P, q, in, out, in_len);
         log.push_back({S, nb, rb, ms});
         if (ms < kTuneMargin * best_ms) {
@@ -500,19 +515,12 @@ void setup_typed(lp_problem *P, const HostSliced &HK, const HostSliced &HT, cons
     auto tvec = [&](int64_t len) { return (T *)P->dalloc(sizeof(T) * (size_t)std::max<int64_t>(len, 1)); };
     P->tmp_n = tvec(n);
     P->tmp_m = tvec(m);
-    // row sums split by entries where a product has enough row blocks to
-    // fill the GPU (split_sums -1), or as asked (0 or 1)
-    auto split_of = [&](const HostSliced &H) {
-        return P->opt.split_sums == -1 ? (int)(H.blk.size() >= (size_t)kSplitMinBlocks) : P->opt.split_sums;
-    };
-    const int split_K = split_of(HK), split_KT = split_of(HT);
     if (P->opt.autotune && !P->ws) {
-        d.K = tuned_sliced<T>(P, HK, rp, ci, kv64, (T *)P->tmp_n, (T *)P->tmp_m, n, P->tune_log_K, P->shape_K, split_K);
-        d.KT = tuned_sliced<T>(P, HT, tp, ti, tv64, (T *)P->tmp_m, (T *)P->tmp_n, m, P->tune_log_KT, P->shape_KT,
-                               split_KT);
+        d.K = tuned_sliced<T>(P, HK, rp, ci, kv64, (T *)P->tmp_n, (T *)P->tmp_m, n, P->tune_log_K, P->shape_K);
+        d.KT = tuned_sliced<T>(P, HT, tp, ti, tv64, (T *)P->tmp_m, (T *)P->tmp_n, m, P->tune_log_KT, P->shape_KT);
     } else {
-        d.K = upload_sliced<T>(P, HK, kv64, split_K);
-        d.KT = upload_sliced<T>(P, HT, tv64, split_KT);
+        d.K = upload_sliced<T>(P, HK, kv64);
+        d.KT = upload_sliced<T>(P, HT, tv64);
         P->shape_K[0] = HK.S; P->shape_K[1] = HK.nb; P->shape_K[2] = HK.rb;
         P->shape_KT[0] = HT.S; P->shape_KT[1] = HT.nb; P->shape_KT[2] = HT.rb;
     }
@@ -596,7 +604,7 @@ int check_options(const lp_options &o)
 }
 
 // The host layout lp_load builds for K (sorted rows, transpose, slices).
-void host_layout(const lp_csr *K, bool mixed, int slice_kib, std::vector<int> &rp, std::vector<int> &ci,
+void host_layout(const lp_csr *K, bool mixed, int slice_kib, int split, std::vector<int> &rp, std::vector<int> &ci,
                  std::vector<double> &kv, std::vector<int> &tp, std::vector<int> &ti, std::vector<double> &tv,
                  HostSliced &HK, HostSliced &HT)
 {
@@ -606,8 +614,8 @@ void host_layout(const lp_csr *K, bool mixed, int slice_kib, std::vector<int> &r
     // column slices sized so a slice of the gathered vector stays in one XCD's L2
     const int64_t tsz = mixed ? 4 : 8;
     const int64_t slice_bytes = (int64_t)slice_kib * 1024;
-    build_sliced(HK, (int)m, (int)n, rp, ci, slices_for(n * tsz, slice_bytes));
-    build_sliced(HT, (int)n, (int)m, tp, ti, slices_for(m * tsz, slice_bytes));
+    build_sliced(HK, (int)m, (int)n, rp, ci, slices_for(n * tsz, slice_bytes), split);
+    build_sliced(HT, (int)n, (int)m, tp, ti, slices_for(m * tsz, slice_bytes), split);
 }
 
 // Every device allocation do_load and setup_typed make, in bytes as dalloc
@@ -659,7 +667,7 @@ int do_load(lp_problem *P, const lp_csr *K, const double *c, const double *q, co
     std::vector<int> rp, ci, tp, ti;
     std::vector<double> kv, tv;
     HostSliced HK, HT;
-    host_layout(K, P->mixed, P->opt.slice_kib, rp, ci, kv, tp, ti, tv, HK, HT);
+    host_layout(K, P->mixed, P->opt.slice_kib, P->opt.split_sums, rp, ci, kv, tp, ti, tv, HK, HT);
     P->slices_K = HK.S;
     P->slices_KT = HT.S;
     if (P->ws && P->ws_size < load_plan_bytes(m, n, nnz, HK, HT, P->mixed)) {
@@ -1311,7 +1319,7 @@ int lp_workspace_size(const lp_csr *K, const lp_options *opt, size_t *bytes)
         std::vector<int> rp, ci, tp, ti;
         std::vector<double> kv, tv;
         HostSliced HK, HT;
-        host_layout(&P, o.precision == LP_MIXED, o.slice_kib, rp, ci, kv, tp, ti, tv, HK, HT);
+        host_layout(&P, o.precision == LP_MIXED, o.slice_kib, o.split_sums, rp, ci, kv, tp, ti, tv, HK, HT);
         *bytes = load_plan_bytes(K->m, K->n, K->nnz, HK, HT, o.precision == LP_MIXED);
     } catch (const HipError &) {
         return LP_ERR_HIP;

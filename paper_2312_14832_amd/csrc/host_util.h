@@ -127,15 +127,13 @@ void append_sorted_rows(const lp_csr *K, int col_off, std::vector<int> &rp, std:
 void transpose_csr(int rows, int cols, const std::vector<int> &rp, const std::vector<int> &ci,
                    const std::vector<double> &v, std::vector<int> &tp, std::vector<int> &ti, std::vector<double> &tv);
 
-// CSR-Stream row blocks of rows [r_begin, r_end): at most kStreamRB rows and
-// nb_max (<= kStreamNB) nonzeros each (a longer single row is a block of its
-// own).  Appends block end rows to `ends` (the first block starts at r_begin).
-// Row blocks of rows [r_begin, r_end): runs of rows of at most kWaveRow
-// entries (at most rb_max rows and nb_max entries), and groups of up to
-// kBlock/64 longer rows (at most nb_max entries; a row longer than that is a
-// block of its own).  ends[k] is the end row of block k; wave[k] = 1 marks a
+// CSR-Stream row blocks of rows [r_begin, r_end): runs of short rows (at most
+// short_max entries each; at most rb_max <= kStreamRB rows and nb_max <=
+// kStreamNB entries), and groups of up to kBlock/64 longer rows (at most
+// nb_max entries; a row longer than that is a block of its own).  ends[k] is
+// the end row of block k (the first starts at r_begin); wave[k] = 1 marks a
 // group of long rows.
 void row_blocks(const int *rp, int r_begin, int r_end, std::vector<int> &ends, std::vector<char> &wave,
-                int nb_max = kStreamNB, int rb_max = kStreamRB);
+                int nb_max = kStreamNB, int rb_max = kStreamRB, int short_max = kWaveRow);
 
 }  // namespace pdlp

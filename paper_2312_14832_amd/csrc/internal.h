@@ -18,6 +18,7 @@ constexpr int kXcds = 8;         // MI355X: 8 XCDs, workgroups dealt to them rou
 constexpr int kStreamNB = 2048;  // nonzeros staged in LDS per row block
 constexpr int kStreamRB = 1024;  // most rows per row block (each thread sums every 256th row)
 constexpr int kWaveRow = 64;     // rows longer than this are summed by a whole wavefront
+constexpr int kMixRow = 256;     // with the row sums split by entries, rows up to this stay among the short ones
 constexpr int kLongRow = 4 * kStreamNB;  // rows longer than this are cut into chunks
 constexpr int kSmall = 1024;     // threads of the one workgroup that runs a small LP's whole loop
 constexpr int kSmallReg = 512;   // threads of its registers-per-thread form (two columns and rows each at most)
@@ -25,7 +26,8 @@ constexpr size_t kSmallStageMax = 150 * 1024;   // dynamic LDS of the staged loo
 constexpr size_t kSmallRegLds = 156 * 1024;     // dynamic LDS of the registers-per-thread loop (stage + table)
 constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;  // device scratch of lp_spmv_noalloc (64 MiB per GPU)
 // A row block is either a run of rows of at most kWaveRow entries (thread per
-// row) or up to kBlock/64 longer rows (wavefront per row); a wavefront block's
+// row; of at most kMixRow, when the row sums are split by entries, which any
+// row length suits) or up to kBlock/64 longer rows (wavefront per row); a wavefront block's
 // end row is stored complemented (~end) in the block descriptor.  A row of
 // more than kLongRow entries (a dense row, e.g. a sum-to-one constraint) is
 // instead cut, in every slice, into chunks of at most one block's nonzeros;
