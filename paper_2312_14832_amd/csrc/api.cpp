@@ -209,9 +209,11 @@ void build_sliced(HostSliced &H, int rows, int cols, const std::vector<int> &rp,
         for (const auto &b : bs) n += b.size();
         return n;
     };
-    const size_t apart = split == 1 ? 0 : cut(kWaveRow);
-    H.split = split == -1 ? apart >= kSplitMinBlocks : split;
-    if (H.split) cut(kMixRow);
+    const size_t apart = cut(kWaveRow);
+    H.split = split == -1 ? apart >= kSplitMinBlocks * (size_t)(kStreamNB / nb) : split;
+    // (a few long rows cost nothing: under a quarter more blocks, they keep
+    // their wavefronts)
+    if (H.split && 4 * apart <= 5 * cut(kMixRow)) cut(kWaveRow);
     // row starts relative to their block (a block holds at most kStreamNB
     // entries unless it is a single row, so the offsets fit 16 bits)
     H.ro.assign((size_t)S * (size_t)rows, 0);
@@ -379,6 +381,8 @@ Sliced<T> upload_sliced(lp_problem *P, const HostSliced &H, const double *scaled
     Sliced<T> q{};
     q.S = H.S;
     q.split = H.split;
+    q.nb = H.nb;
+    q.nblk = (int)H.blk.size();
     q.rows = H.rows;
     q.grid = partial_grid(H.S, H.max_blocks);
     int *rp = (int *)P->dalloc(sizeof(int) * H.rp.size());
@@ -544,11 +548,11 @@ void setup_typed(lp_problem *P, const HostSliced &HK, const HostSliced &HT, cons
     d.xa = tvec(n); d.ya = tvec(m); d.Kxa = tvec(m); d.KTya = tvec(n);
     d.x0 = tvec(n); d.y0 = tvec(m); d.Kx0 = tvec(m); d.KTy0 = tvec(n);
     d.xo = tvec(n); d.yo = tvec(m); d.KTyo = tvec(n);
-    d.part_primal = (double *)P->dalloc(sizeof(double) * kMaxGrid);
+    d.part_primal = (double *)P->dalloc(sizeof(double) * kMaxGrid * 2);   // two copies, as the controller below
     d.part_dual = (double *)P->dalloc(sizeof(double) * kMaxGrid * 2);
     d.part_check = (double *)P->dalloc(sizeof(double) * kMaxGrid * kCheckSums);
     d.part_ray = (double *)P->dalloc(sizeof(double) * kMaxGrid * kRaySums);
-    d.ctl = (Ctl *)P->dalloc(sizeof(Ctl));
+    d.ctl = (Ctl *)P->dalloc(2 * sizeof(Ctl));   // two copies: the fused slot's controller goes from one to the other
 }
 
 // Host copies of lp_load's arrays when the caller passed device pointers.
@@ -614,8 +618,15 @@ void host_layout(const lp_csr *K, bool mixed, int slice_kib, int split, std::vec
     // column slices sized so a slice of the gathered vector stays in one XCD's L2
     const int64_t tsz = mixed ? 4 : 8;
     const int64_t slice_bytes = (int64_t)slice_kib * 1024;
-    build_sliced(HK, (int)m, (int)n, rp, ci, slices_for(n * tsz, slice_bytes), split);
-    build_sliced(HT, (int)n, (int)m, tp, ti, slices_for(m * tsz, slice_bytes), split);
+    const int SK = slices_for(n * tsz, slice_bytes), ST = slices_for(m * tsz, slice_bytes);
+    // Two single slices run the fused slot, whose two kernels are over in a
+    // few microseconds: blocks small enough for 512 workgroups (at least 512
+    // nonzeros each; 23,457 columns and 140,742 nonzeros: 275 blocks, where
+    // 2048-entry ones left 187 of the 256 CUs idle).
+    const bool one = SK == 1 && ST == 1;
+    const int nb = !one || K->nnz > 512 * 1024 ? kStreamNB : K->nnz > 512 * 512 ? 1024 : 512;
+    build_sliced(HK, (int)m, (int)n, rp, ci, SK, split, nb, one ? kFusedRB : kStreamRB);
+    build_sliced(HT, (int)n, (int)m, tp, ti, ST, split, nb, one ? kFusedRB : kStreamRB);
 }
 
 // Every device allocation do_load and setup_typed make, in bytes as dalloc
@@ -650,8 +661,8 @@ size_t load_plan_bytes(int64_t m, int64_t n, int64_t nnz, const HostSliced &HK, 
     if (mixed) for (int64_t len : {n, n, n, m}) add(T * one(len));
     for (int k = 0; k < 2; ++k) for (int64_t len : {n, m, m, n}) add(T * one(len));
     for (int64_t len : {n, m, m, n, n, m, m, n, n, m, n}) add(T * one(len));   // averages, anchor (+ products), output
-    add(8 * kMaxGrid); add(8 * kMaxGrid * 2); add(8 * kMaxGrid * kCheckSums); add(8 * kMaxGrid * kRaySums);
-    add(sizeof(Ctl));
+    add(8 * kMaxGrid * 2); add(8 * kMaxGrid * 2); add(8 * kMaxGrid * kCheckSums); add(8 * kMaxGrid * kRaySums);
+    add(2 * sizeof(Ctl));
     // mixed precision: the FP64 re-check keeps the CSR pair above and adds its products and partials
     if (mixed) {
         for (int64_t len : {m, m, n, n}) add(8 * one(len));
@@ -751,6 +762,14 @@ int do_load(lp_problem *P, const lp_csr *K, const double *c, const double *q, co
     g.vb_n = (int)((n + kBlock - 1) / kBlock);
     g.vb_m = (int)((m + kBlock - 1) / kBlock);
     g.grid = std::max(1, std::min(kMaxGrid, g.vb_n + g.vb_m));
+    // the fused slot: its second kernel's workgroups are the slots of every
+    // partial sum but the dual step's
+    auto fits = [](const auto &A, const int *shape) { return A.S == 1 && A.nlong == 0 && shape[2] <= kFusedRB; };
+    auto blocks = [&](bool t) { return P->mixed ? (t ? P->d32.KT.nblk : P->d32.K.nblk) : (t ? P->d64.KT.nblk : P->d64.K.nblk); };
+    g.fused = P->mixed ? fits(P->d32.K, P->shape_K) && fits(P->d32.KT, P->shape_KT)
+                       : fits(P->d64.K, P->shape_K) && fits(P->d64.KT, P->shape_KT);
+    g.grid_K = std::max(1, std::min(kMaxGrid, blocks(false)));
+    if (g.fused) g.grid = std::max(1, std::min(kMaxGrid, std::max(blocks(true), g.vb_m)));
     return LP_OK;
 }
 
@@ -758,23 +777,55 @@ int do_load(lp_problem *P, const lp_csr *K, const double *c, const double *q, co
 // solve
 // ---------------------------------------------------------------------------
 
-template <typename T>
-void launch_slot(lp_problem *P, int slot, bool timed)
+// Slots between check kernels: the largest divisor of check_every up to 8.
+// Without rejected attempts a check then falls due just where its kernels
+// are; each rejection leaves up to 7 slots idle until they come.  The two
+// kernels cost 4 (medium LPs) to 10 us a slot when they had nothing to do.
+int check_group(const lp_problem *P)
 {
-    Dev<T> &d = P->dev<T>();
+    int G = std::min(8, P->opt.check_every);
+    while (P->opt.check_every % G) --G;
+    return G;
+}
+
+// Slot `slot` of a window of W; timed: every slot has the check kernels, so
+// that all of them do real work
+template <typename T>
+void launch_slot(lp_problem *P, int slot, int W, bool timed)
+{
+    Dev<T> d = P->dev<T>();
     hipStream_t st = P->stream;
+    const bool checks = timed || (slot + 1) % check_group(P) == 0 || slot + 1 == W;
     if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 0], st));
-    HIPT(launch_partial_K<T>(d, st));
-    HIPT(launch_dual<T>(d, P->geo, st));
-    if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 1], st));
-    HIPT(launch_step_decide<T>(d, P->geo, st));
-    if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 2], st));
-    HIPT(launch_partial_KT<T>(d, st));
-    HIPT(launch_update<T>(d, P->geo, st));
+    if (P->geo.fused) {
+        const int a = slot & 1, b = a ^ 1;
+        Ctl *in = d.ctl + a, *out = d.ctl + b;
+        const double *part_in = d.part_primal + a * kMaxGrid;
+        d.part_primal += b * kMaxGrid;
+        HIPT(launch_fused_dual<T>(d, P->geo, in, st));
+        if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 1], st));
+        if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 2], st));
+        HIPT(launch_fused_update<T>(d, P->geo, in, part_in, out, st));
+        d.ctl = out;
+    } else {
+        HIPT(launch_partial_K<T>(d, st));
+        HIPT(launch_dual<T>(d, P->geo, st));
+        if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 1], st));
+        HIPT(launch_step_decide<T>(d, P->geo, st));
+        if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 2], st));
+        HIPT(launch_partial_KT<T>(d, st));
+        HIPT(launch_update<T>(d, P->geo, st));
+    }
     if (timed) HIPT(hipEventRecord(P->ev[4 * slot + 3], st));
     // the check sums of a check step come from the update kernel itself
-    HIPT(launch_check_decide<T>(d, P->geo, P->Nq, P->Nc, st));
-    HIPT(launch_check_apply<T>(d, P->geo, st));
+    if (checks) {
+        HIPT(launch_check_decide<T>(d, P->geo, P->Nq, P->Nc, st));
+        HIPT(launch_check_apply<T>(d, P->geo, st));
+    }
+    // the host and the next window find them in the first copies
+    const Dev<T> &first = P->dev<T>();
+    if (slot + 1 == W && d.ctl != first.ctl)
+        HIPT(launch_copy_ctl(d.ctl, d.part_primal, first.ctl, first.part_primal, st));
 }
 
 template <typename T>
@@ -993,7 +1044,7 @@ int do_solve(lp_problem *P, double tol, int64_t max_iters, double time_limit)
         HIPT(hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed));
         bool ok = true;
         try {
-            for (int s = 0; s < W; ++s) launch_slot<T>(P, s, timed_graph);
+            for (int s = 0; s < W; ++s) launch_slot<T>(P, s, W, timed_graph);
         } catch (const HipError &) {
             ok = false;
         }
@@ -1017,7 +1068,7 @@ int do_solve(lp_problem *P, double tol, int64_t max_iters, double time_limit)
         if (use_graph && !sampled) {
             HIPT(hipGraphLaunch(P->graph, st));
         } else {
-            for (int s = 0; s < W; ++s) launch_slot<T>(P, s, timed_now);
+            for (int s = 0; s < W; ++s) launch_slot<T>(P, s, W, timed_now);
         }
         get_ctl(P, d.ctl);
         resolve_confirm<T>(P);

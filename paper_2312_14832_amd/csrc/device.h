@@ -35,20 +35,65 @@ __device__ __forceinline__ double proj_lambda(double g, bool lf, bool uf)
     return g;
 }
 
-// One FP64 partial per workgroup and value: wave64 butterfly, then the four
-// wave results added in a fixed order.
-template <int NV>
+// v of the lane that DPP control CTRL names, 0 where it names none
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ float dpp_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
+}
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true));
+}
+__device__ __forceinline__ float lane63(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ double lane63(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// The sum of v over the wavefront's 64 lanes, in every lane, in a fixed order:
+// lanes shifted down each row of 16 by 1, 2, 4 and 8, then the rows' last
+// lanes broadcast into the rows after them.  These moves stay in the vector
+// registers; a butterfly of __shfl_xor goes through the LDS unit (two
+// ds_bpermute a step for a double, each a round trip of about 100 cycles).
+// Every lane of the wavefront must call it.
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v)
+{
+    v += dpp_move<0x111>(v);        // row_shr:1
+    v += dpp_move<0x112>(v);        // row_shr:2
+    v += dpp_move<0x114>(v);        // row_shr:4
+    v += dpp_move<0x118>(v);        // row_shr:8
+    v += dpp_move<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v += dpp_move<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return lane63(v);
+}
+
+// the same by a butterfly of __shfl_xor
+template <typename T>
+__device__ __forceinline__ T wave_butterfly(T v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+// One FP64 partial per workgroup and value: each wavefront's sum, then the
+// four added in a fixed order.  FAST: by wave_sum, in kernels that last a few
+// microseconds; in the large ones the order of the sums stays the butterfly's.
+template <int NV, bool FAST = false>
 __device__ __forceinline__ void block_store_partials(double (&v)[NV], double *out, int slot = -1)
 {
     __shared__ double sh[kBlock / 64][NV];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        double a = v[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-        v[i] = a;
-    }
+    for (int i = 0; i < NV; ++i) v[i] = FAST ? wave_sum(v[i]) : wave_butterfly(v[i]);
     if (lane == 0) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) sh[wave][i] = v[i];
@@ -91,10 +136,7 @@ __device__ __forceinline__ void block_sum_partials(const double *part, int np, d
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc[i] += __shfl_xor(acc[i], off);
-    }
+    for (int i = 0; i < NV; ++i) acc[i] = wave_butterfly(acc[i]);
     if (lane == 0) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) sh[wave][i] = acc[i];
@@ -193,8 +235,7 @@ __device__ __forceinline__ bool long_row_total(const Sliced<T> &P, int vb, T &va
     for (int k = a; k < P.nlong && P.lrow[k] < hi; ++k) {
         double acc = 0.0;
         for (int p = P.loff[k] + (int)threadIdx.x; p < P.loff[k + 1]; p += kBlock) acc += (double)P.lpart[p];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+        acc = wave_butterfly(acc);
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
         __syncthreads();
         if (P.lrow[k] - lo == (int)threadIdx.x) {
@@ -432,6 +473,7 @@ __device__ inline void step_decision_f(Ctl *ctl, double dx2, double dy2, double 
         ctl->numerical = 1;
         ctl->accepted = 0;
         ctl->mode = MODE_CHECK;
+        ctl->hold = 1;
         return;
     }
     const bool accept = rule == 1;
@@ -448,6 +490,7 @@ __device__ inline void step_decision_f(Ctl *ctl, double dx2, double dy2, double 
         ctl->accepted = 0;
         ctl->mode = MODE_NONE;
     }
+    ctl->hold = ctl->mode == MODE_CHECK;
     ctl->eta = eta_new;
 }
 
@@ -516,6 +559,7 @@ __device__ inline void check_decision(Ctl *ctl, const double *S, const double *R
     check_quantities(ctl, S, Nq, Nc, rel, kkt);
     const int mode = ctl->mode;
     const int veto = ctl->veto;
+    ctl->hold = 0;
     ctl->veto = 0;
     ctl->restart_to = 0;
     ctl->copy_out = 0;
@@ -694,7 +738,8 @@ struct RowsRel {
 };
 
 // LDS of the split row sums of a block of short rows (stream_block, SPLIT).
-// Thread t walks the products of chunk t, entries [8t, 8t + 8) of the block.
+// Thread t walks the products of chunk t, entries [U t, U t + U) of the block
+// (U = 8 in a full-sized block).
 template <typename T>
 struct SplitLds {
     unsigned short rend[kStreamRB];   // each row's end, relative to the block's first entry
@@ -774,7 +819,7 @@ __device__ __forceinline__ void split_row_sums(const int (&rs)[RU], const int (&
 // In a block of short rows (at most kStreamRB) each thread sums every
 // kBlock-th row in index order; with SPLIT the sums are split by entries
 // instead, so that a few long rows among short ones do not hold up their
-// wavefront: thread t adds up the products of chunk t (8 entries) row by
+// wavefront: thread t adds up the products of chunk t (U entries) row by
 // row, a row that lies wholly in the chunk is finished there, and a row that
 // crosses chunks is finished by the thread holding its last entry, which adds
 // the open parts of the chunks before its own in a fixed order.  Every
@@ -783,22 +828,23 @@ __device__ __forceinline__ void split_row_sums(const int (&rs)[RU], const int (&
 // barrier), then every thread stores its rows as before.  In a block of long
 // rows (wave set, at most kBlock/64) each wavefront sums one row, lanes
 // striding and a butterfly combining them.  A block of one row longer than
-// kStreamNB is summed by the whole workgroup.  Every thread of the workgroup
+// the block's nonzeros is summed by the whole workgroup.  Every thread of the workgroup
 // must call it.
-template <bool SPLIT = false, typename T, typename ROWS>
+template <bool SPLIT = false, int U = kStreamNB / kBlock, typename T, typename ROWS>
 __device__ __forceinline__ void stream_block(const ROWS &rows, const int *__restrict__ ci,
                                              const T *__restrict__ v, const T *__restrict__ x, int r0, int r1,
                                              bool wave, int b, int e, T *__restrict__ out, T *prod, double *red,
                                              SplitLds<T> *L = nullptr)
 {
     const int cnt = e - b;
-    // a multi-row block never exceeds kStreamNB nonzeros, only a single row can
-    if (cnt <= kStreamNB) {
+    // a multi-row block never exceeds its product's nonzeros per block (U to a
+    // thread), only a single row can
+    if (cnt <= U * kBlock) {
         // Straight-line phases so that a thread's loads overlap: every value,
         // column and row pointer it owns, then every gather, then the
         // products.  Slots past the block's end re-read its last entry or row
         // (same cache line) rather than branch, which would serialise them.
-        constexpr int U = kStreamNB / kBlock, RU = kStreamRB / kBlock;
+        constexpr int RU = kStreamRB / kBlock;
         int col[U], rs[RU], re[RU];
         T a[U], g[U];
         if (cnt > 0) {
@@ -855,9 +901,12 @@ __device__ __forceinline__ void stream_block(const ROWS &rows, const int *__rest
             if (r < r1) {   // uniform over the wavefront
                 const int p1 = rows.end(r, r1, b, e) - b;
                 T acc = T(0);
+                // (with wave_sum here the large products' kernels need 94
+                // registers instead of 106, run five waves a SIMD instead of
+                // four, and are 2-6% slower: the gathers of more waves crowd
+                // the L2)
                 for (int p = rows.start(r, b) - b + lane; p < p1; p += 64) acc += prod[p];
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+                acc = wave_butterfly(acc);
                 if (lane == 0) out[r] = acc;
             }
         }
@@ -865,8 +914,7 @@ __device__ __forceinline__ void stream_block(const ROWS &rows, const int *__rest
     } else {
         T acc = T(0);
         for (int t = b + (int)threadIdx.x; t < e; t += kBlock) acc += v[t] * x[ci[t]];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+        acc = wave_butterfly(acc);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = (double)acc;
         __syncthreads();
         if (threadIdx.x == 0) out[r0] = (T)(((red[0] + red[1]) + red[2]) + red[3]);
@@ -898,8 +946,7 @@ __device__ __forceinline__ T chunk_dot(const int *__restrict__ ci, const T *__re
 #pragma unroll
     for (int u = 0; u < U; ++u)
         if ((int)threadIdx.x + u * kBlock < cnt) acc += a[u] * g[u];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    acc = wave_butterfly(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = (double)acc;
     __syncthreads();
     const T r = (T)(((red[0] + red[1]) + red[2]) + red[3]);
@@ -955,10 +1002,10 @@ __device__ __forceinline__ void ray_sums_pass(const Dev<T> &d, int c, int vb_n, 
 // One column slice's partial products (see Sliced): workgroup b takes slice
 // b % S and walks that slice's row blocks with stride gridDim / S.  LONG:
 // the product has long rows, so some blocks are chunks of one.
-template <bool LONG, bool SPLIT = false, typename T>
+template <bool LONG, bool SPLIT = false, int U = kStreamNB / kBlock, typename T>
 __device__ __forceinline__ void sliced_partial(const Sliced<T> &P, const T *__restrict__ x)
 {
-    __shared__ T prod[kStreamNB];
+    __shared__ T prod[U * kBlock];
     __shared__ double red[kBlock / 64];
     SplitLds<T> *split = nullptr;
     if constexpr (SPLIT) {
@@ -982,7 +1029,7 @@ __device__ __forceinline__ void sliced_partial(const Sliced<T> &P, const T *__re
             }
         }
         const bool wave = q.y < 0;
-        stream_block<SPLIT>(rows, P.ci, P.v, x, q.x, wave ? ~q.y : q.y, wave, q.z, q.w, out, prod, red, split);
+        stream_block<SPLIT, U>(rows, P.ci, P.v, x, q.x, wave ? ~q.y : q.y, wave, q.z, q.w, out, prod, red, split);
     }
 }
 

@@ -17,6 +17,7 @@ constexpr int kRaySums = 4;      // the current iterate's rays (difference from 
 constexpr int kXcds = 8;         // MI355X: 8 XCDs, workgroups dealt to them round-robin
 constexpr int kStreamNB = 2048;  // nonzeros staged in LDS per row block
 constexpr int kStreamRB = 1024;  // most rows per row block (each thread sums every 256th row)
+constexpr int kFusedRB = 512;    // most rows per row block of a product run by the fused slot (two to a thread)
 constexpr int kWaveRow = 64;     // rows longer than this are summed by a whole wavefront
 constexpr int kMixRow = 256;     // with the row sums split by entries, rows up to this stay among the short ones
 constexpr int kLongRow = 4 * kStreamNB;  // rows longer than this are cut into chunks
@@ -46,6 +47,8 @@ constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;  // device scratch of 
 template <typename T>
 struct Sliced {
     int S;            // column slices (a power of two)
+    int nb;           // most nonzeros of one row block (unless a single row)
+    int nblk;         // row blocks in total
     int rows;         // rows of the product
     int grid;         // workgroups of the partial pass (a multiple of 8 and of S)
     const int *rp;    // [S*(rows+1)] per-slice row pointers into ci / v (the one-workgroup loop's CSR)
@@ -104,6 +107,12 @@ struct Ctl {
     int conf_mode;     // the check mode that passed the test
     int veto;          // run the next check decision without its termination test (re-check failed)
     long long confirms;  // FP64 re-checks made
+    // Single-LP launches run the check kernels only after every few slots: a
+    // step that makes a check due sets hold, which keeps the slots after it
+    // idle until the check decision has run.
+    int hold;
+    int idle;            // this slot is one of those (set by k_step_decide)
+    double f_lo, f_hi;   // step_factors of k, for the fused slot's decision (written by its first kernel)
 };
 
 template <typename T>
@@ -119,7 +128,7 @@ struct Dev {
     T *x0, *y0;                // restart anchor
     T *Kx0, *KTy0;             // K x0 and K' y0 (ray residuals are differences of products)
     T *xo, *yo, *KTyo;         // returned point
-    double *part_primal;       // [kMaxGrid]      |x' - x|^2 partials
+    double *part_primal;       // [kMaxGrid]      |x' - x|^2 partials (a single LP has two, see launch_fused_update)
     double *part_dual;         // [kMaxGrid * 2]  |y' - y|^2, (y'-y).(Kx'-Kx)
     double *part_check;        // [kMaxGrid * kCheckSums]
     double *part_ray;          // [kMaxGrid * kRaySums] (a pass of its own: fewer live registers)
@@ -141,6 +150,8 @@ struct Conf64 {
 struct Geo {
     int grid;                  // workgroups of the elementwise solver kernels
     int vb_n, vb_m;            // 256-element chunks of the n- and m-vectors
+    int fused;                 // the slot's products and steps are one kernel each (see launch_fused_dual)
+    int grid_K;                // workgroups of the first of them (the second's are `grid`)
 };
 
 // Row blocks of one product of a batch, dealt to XCDs by instance: the
@@ -276,6 +287,17 @@ hipError_t launch_small_loop_batch(const Dev<T> *devs, const double *nq, const d
 template <typename T>
 hipError_t launch_gather_probe(const int *idx, const T *x, int64_t per_slice, int S, int64_t slice_len, T *out,
                                int grid, hipStream_t s);
+// A slot of an LP whose products are one column slice each without long rows,
+// in two kernels: K x' with the dual step, then the step decision with K'y',
+// the averages and the next primal trial.  The controller goes from one copy
+// to another: the second kernel's workgroups all read `in` and take the same
+// decision, one of them writes `out`.  So do the |x' - x|^2 partials
+// (d.part_primal is where they go): every workgroup reads them all, and the
+// first to finish must not overwrite what another has yet to read.
+template <typename T> hipError_t launch_fused_dual(const Dev<T> &d, const Geo &g, Ctl *ctl, hipStream_t s);
+template <typename T> hipError_t launch_fused_update(const Dev<T> &d, const Geo &g, const Ctl *in, const double *part_in,
+                                                     Ctl *out, hipStream_t s);
+hipError_t launch_copy_ctl(const Ctl *in, const double *part_in, Ctl *out, double *part_out, hipStream_t s);
 template <typename T> hipError_t launch_partial_K(const Dev<T> &d, hipStream_t s);
 template <typename T> hipError_t launch_partial_KT(const Dev<T> &d, hipStream_t s);
 template <typename T> hipError_t launch_dual(const Dev<T> &d, const Geo &g, hipStream_t s);

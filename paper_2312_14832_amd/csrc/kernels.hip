@@ -44,7 +44,7 @@ template <typename T, bool LONG, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_partial_K(Dev<T> d)
 {
     const Ctl *ctl = d.ctl;
-    if (ctl->done) return;
+    if (ctl->done || ctl->hold) return;
     sliced_partial<LONG, SPLIT>(d.K, (const T *)pick(d.xb, ctl->cur ^ 1));
 }
 
@@ -53,7 +53,7 @@ template <typename T, bool LONG, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_partial_KT(Dev<T> d)
 {
     const Ctl *ctl = d.ctl;
-    if (ctl->done || !ctl->accepted) return;
+    if (ctl->done || ctl->idle || !ctl->accepted) return;
     sliced_partial<LONG, SPLIT>(d.KT, (const T *)pick(d.yb, ctl->cur));
 }
 
@@ -61,7 +61,7 @@ template <typename T, int NS, bool LONG>
 __global__ __launch_bounds__(kBlock) void k_dual(Dev<T> d, int vb_m)
 {
     const Ctl *ctl = d.ctl;
-    if (ctl->done) return;
+    if (ctl->done || ctl->hold) return;
     const int c = ctl->cur;
     const T sigma = (T)(ctl->eta * ctl->omega);
     DualEpi<T> epi{pick(d.yb, c), pick(d.Kxb, c), d.qs, pick(d.yb, c ^ 1), pick(d.Kxb, c ^ 1), d.m1, sigma, 0.0, 0.0};
@@ -79,14 +79,18 @@ __global__ __launch_bounds__(kBlock) void k_dual(Dev<T> d, int vb_m)
 // the rule).  eta_bar = (omega|dx|^2 + |dy|^2/omega) / (2|dy.K dx|).
 __global__ __launch_bounds__(kBlock) void k_step_decide(Ctl *ctl, const double *pp, const double *pd, int np)
 {
-    if (ctl->done) {
-        if (threadIdx.x == 0) ctl->mode = MODE_NONE;
+    if (ctl->done || ctl->hold) {
+        if (threadIdx.x == 0) {
+            if (ctl->done) ctl->mode = MODE_NONE;
+            ctl->idle = 1;
+        }
         return;
     }
     double a[1], b[2];
     block_sum_partials<1>(pp, np, a);
     block_sum_partials<2>(pd, np, b);
     if (threadIdx.x != 0) return;
+    ctl->idle = 0;
     step_decision(ctl, a[0], b[0], b[1]);
 }
 
@@ -94,7 +98,7 @@ template <typename T, int NS, bool LONG>
 __global__ __launch_bounds__(kBlock) void k_update(Dev<T> d, int vb_n, int vb_m)
 {
     const Ctl *ctl = d.ctl;
-    if (ctl->done) return;
+    if (ctl->done || ctl->idle) return;
     const int c = ctl->cur;
     const T tau = (T)(ctl->eta / ctl->omega);
     double dx2 = 0.0;
@@ -194,8 +198,7 @@ __global__ __launch_bounds__(kBlock) void k_csr64(const int *__restrict__ rp, co
         double acc = 0.0;
         const int e = rp[r + 1];
         for (int p = rp[r] + lane; p < e; p += 64) acc += v[p] * (double)x[ci[p]];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+        acc = wave_butterfly(acc);
         if (lane == 0) out[r] = acc;
     }
 }
@@ -280,6 +283,229 @@ __global__ __launch_bounds__(kBlock) void k_confirm_decide(Ctl *ctl, const doubl
 }
 
 // ----------------------------------------------------------------------------
+// the slot in two kernels
+// ----------------------------------------------------------------------------
+
+// With one column slice and no long rows the row sums are complete in the
+// workgroup that makes them, so each product's step follows there, and the
+// step decision is taken by every workgroup of the second kernel for itself
+// (the partials it adds are 3 doubles per workgroup of the kernels before).
+// What bounds such a slot is launches: at 23,457 columns and 140,742 nonzeros
+// seven kernels of 1.3 to 4.8 us took 22 us.
+
+// LDS of one fused kernel
+template <typename T, int U>
+struct FusedLds {
+    T prod[U * kBlock];
+    T row[kFusedRB];   // the block's row sums
+    double red[kBlock / 64];
+};
+
+// the row sums of block q of a single-slice product, to L.row
+template <bool SPLIT, int U, typename T>
+__device__ __forceinline__ void fused_rows(const Sliced<T> &P, const T *__restrict__ x, const int4 &q, FusedLds<T, U> &L,
+                                           SplitLds<T> *split)
+{
+    const bool wave = q.y < 0;
+    stream_block<SPLIT, U>(RowsRel{P.ro}, P.ci, P.v, x, q.x, wave ? ~q.y : q.y, wave, q.z, q.w, L.row - q.x, L.prod,
+                           L.red, split);
+}
+
+// K x' and the dual step.  The last workgroup makes the step rule's factors
+// for the second kernel (two pow calls that no other workgroup waits for).
+template <typename T, int U, bool SPLIT>
+__global__ __launch_bounds__(kBlock) void k_fused_dual(Dev<T> d, Ctl *ctl)
+{
+    __shared__ FusedLds<T, U> L;
+    SplitLds<T> *split = nullptr;
+    if constexpr (SPLIT) {
+        __shared__ SplitLds<T> split_lds;
+        split = &split_lds;
+    }
+    if (ctl->done || ctl->hold) return;
+    const int blocks = (int)gridDim.x - 1;
+    if ((int)blockIdx.x == blocks) {
+        if (threadIdx.x == 0 && !ctl->fixed_step) step_factors(ctl->k, ctl->f_lo, ctl->f_hi);
+        return;
+    }
+    const int c = ctl->cur;
+    const T sigma = (T)(ctl->eta * ctl->omega);
+    DualEpi<T> epi{pick(d.yb, c), pick(d.Kxb, c), d.qs, pick(d.yb, c ^ 1), pick(d.Kxb, c ^ 1), d.m1, sigma, 0.0, 0.0};
+    const T *x = pick(d.xb, c ^ 1);
+    for (int k = blockIdx.x; k < d.K.nblk; k += blocks) {
+        const int4 q = d.K.blk[k];
+        const int r1 = q.y < 0 ? ~q.y : q.y;
+        fused_rows<SPLIT, U>(d.K, x, q, L, split);
+#pragma unroll
+        for (int j = 0; j < kFusedRB / kBlock; ++j) {
+            const int r = q.x + (int)threadIdx.x + j * kBlock;
+            if (r < r1) epi(r, L.row[r - q.x]);
+        }
+    }
+    double v[2] = {epi.dy2, epi.inter};
+    block_store_partials<2, true>(v, d.part_dual);
+}
+
+// The step decision, K'y' of an accepted step with the averages and the next
+// primal trial (after a rejection the new trial from the same point), and the
+// check sums when a check is due.  The product of a workgroup's first block
+// is made before the decision is known (the trial y' is what it gathers from
+// either way), so the partials' loads and the decision hide behind it.
+template <typename T, int U, bool SPLIT>
+__global__ __launch_bounds__(kBlock) void k_fused_update(Dev<T> d, const Ctl *__restrict__ in,
+                                                         const double *__restrict__ part_in, Ctl *__restrict__ out,
+                                                         int np_dual, int vb_m)
+{
+    __shared__ FusedLds<T, U> L;
+    __shared__ double sh[kBlock / 64][3];
+    __shared__ Ctl sc;   // workgroup 0: the controller on its way from in to out
+    SplitLds<T> *split = nullptr;
+    if constexpr (SPLIT) {
+        __shared__ SplitLds<T> split_lds;
+        split = &split_lds;
+    }
+    const int t = (int)threadIdx.x;
+    static_assert(sizeof(Ctl) % sizeof(int) == 0, "copied by words");
+    if (blockIdx.x == 0)
+        for (int w = t; w < (int)(sizeof(Ctl) / sizeof(int)); w += kBlock)
+            reinterpret_cast<int *>(&sc)[w] = reinterpret_cast<const int *>(in)[w];
+    const bool run = !in->done && !in->hold;
+    int c = in->cur;
+    bool accepted = false, primal = true, check = false;
+    T tau = T(0), w = T(0);
+    double dx2 = 0.0;
+    if (run) {
+        // this thread's share of the partials
+        constexpr int PU = kMaxGrid / kBlock;
+        const int np = (int)gridDim.x;
+        double pp[PU], p0[PU], p1[PU];
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+            const int i = t + u * kBlock;
+            pp[u] = i < np ? part_in[i] : 0.0;
+            p0[u] = i < np_dual ? d.part_dual[2 * i] : 0.0;
+            p1[u] = i < np_dual ? d.part_dual[2 * i + 1] : 0.0;
+        }
+        const T *yt = pick(d.yb, c ^ 1);
+        const bool any = (int)blockIdx.x < d.KT.nblk;
+        int4 q = any ? d.KT.blk[blockIdx.x] : make_int4(0, 0, 0, 0);
+        if (any) fused_rows<SPLIT, U>(d.KT, yt, q, L, split);
+        double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+            v[0] += pp[u];
+            v[1] += p0[u];
+            v[2] += p1[u];
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = wave_sum(v[i]);
+        if ((t & 63) == 0) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) sh[t >> 6][i] = v[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = ((sh[0][i] + sh[1][i]) + sh[2][i]) + sh[3][i];
+        double eta_next;
+        const double eta = in->eta, omega = in->omega;
+        const int rule = step_rule(eta, omega, in->fixed_step, v[0], v[1], v[2], in->f_lo, in->f_hi, eta_next);
+        accepted = rule == 1;
+        check = rule < 0 || (accepted && mode_after_accept(in->k + 1, in->check_every, in->max_iters) == MODE_CHECK);
+        primal = !check;
+        if (rule < 0) eta_next = eta;
+        if (accepted) {
+            w = (T)(eta / (in->W + eta));
+            c ^= 1;
+        }
+        tau = (T)(eta_next / omega);
+        if (blockIdx.x == 0 && t == 0) {
+            sc.idle = 0;
+            step_decision_f(&sc, v[0], v[1], v[2], in->f_lo, in->f_hi);
+        }
+        if (!accepted) {
+            for (int k = blockIdx.x; k < d.KT.nblk; k += (int)gridDim.x) {
+                const int4 b = d.KT.blk[k];
+                const int r1 = b.y < 0 ? ~b.y : b.y;
+                for (int r = b.x + t; r < r1; r += kBlock) primal_elem(d, c, tau, r, dx2);
+            }
+        } else {
+            UpdateEpi<T> epi{pick(d.xb, c), d.cs, d.ls, d.us, pick(d.KTyb, c), d.xa, d.KTya, pick(d.xb, c ^ 1), w, tau,
+                             primal, 0.0};
+            for (int k = blockIdx.x; k < d.KT.nblk;) {
+                const int r1 = q.y < 0 ? ~q.y : q.y;
+#pragma unroll
+                for (int j = 0; j < kFusedRB / kBlock; ++j) {
+                    const int r = q.x + t + j * kBlock;
+                    if (r < r1) epi(r, L.row[r - q.x]);
+                }
+                k += (int)gridDim.x;
+                if (k < d.KT.nblk) {   // the same for the whole workgroup
+                    q = d.KT.blk[k];
+                    fused_rows<SPLIT, U>(d.KT, yt, q, L, split);
+                }
+            }
+            for (int vb = blockIdx.x; vb < vb_m; vb += (int)gridDim.x) {
+                const int i = vb * kBlock + t;
+                if (i < d.m) average_row(d, i, c, w);
+            }
+            dx2 = epi.dx2;
+        }
+        double p[1] = {dx2};
+        block_store_partials<1, true>(p, d.part_primal);
+        if (check) {
+            // the sums of the check that follows, each thread over the entries
+            // it has just written
+            double cs[kCheckSums], rs[kRaySums];
+            const T *x = pick(d.xb, c), *kty = pick(d.KTyb, c), *y = pick(d.yb, c), *kx = pick(d.Kxb, c);
+#pragma unroll
+            for (int i = 0; i < kCheckSums; ++i) cs[i] = 0.0;
+            for (int k = blockIdx.x; k < d.KT.nblk; k += (int)gridDim.x) {
+                const int4 b = d.KT.blk[k];
+                const int r1 = b.y < 0 ? ~b.y : b.y;
+                for (int r = b.x + t; r < r1; r += kBlock) {
+                    col_sums(d, r, x, kty, cs);
+                    col_sums(d, r, (const T *)d.xa, (const T *)d.KTya, cs + 9);
+                }
+            }
+            for (int vb = blockIdx.x; vb < vb_m; vb += (int)gridDim.x) {
+                const int i = vb * kBlock + t;
+                if (i < d.m) {
+                    row_sums(d, i, d.m1, y, kx, cs);
+                    row_sums(d, i, d.m1, (const T *)d.ya, (const T *)d.Kxa, cs + 9);
+                }
+            }
+            block_store_partials<kCheckSums, true>(cs, d.part_check);
+#pragma unroll
+            for (int i = 0; i < kRaySums; ++i) rs[i] = 0.0;
+            for (int k = blockIdx.x; k < d.KT.nblk; k += (int)gridDim.x) {
+                const int4 b = d.KT.blk[k];
+                const int r1 = b.y < 0 ? ~b.y : b.y;
+                for (int r = b.x + t; r < r1; r += kBlock) ray_col_sums(d, r, x, kty, rs);
+            }
+            for (int vb = blockIdx.x; vb < vb_m; vb += (int)gridDim.x) {
+                const int i = vb * kBlock + t;
+                if (i < d.m) ray_row_sums(d, i, d.m1, y, kx, rs);
+            }
+            block_store_partials<kRaySums, true>(rs, d.part_ray);
+        }
+    }
+    if (blockIdx.x == 0) {
+        __syncthreads();
+        if (t == 0 && sc.done) sc.mode = MODE_NONE;   // the check that ended the solve was the last
+        __syncthreads();
+        for (int k = t; k < (int)(sizeof(Ctl) / sizeof(int)); k += kBlock)
+            reinterpret_cast<int *>(out)[k] = reinterpret_cast<const int *>(&sc)[k];
+    }
+}
+
+__global__ void k_copy_ctl(const Ctl *in, const double *part_in, Ctl *out, double *part_out)
+{
+    for (int k = threadIdx.x; k < kMaxGrid; k += (int)blockDim.x) part_out[k] = part_in[k];
+    for (int k = threadIdx.x; k < (int)(sizeof(Ctl) / sizeof(int)); k += (int)blockDim.x)
+        reinterpret_cast<int *>(out)[k] = reinterpret_cast<const int *>(in)[k];
+}
+
+// ----------------------------------------------------------------------------
 // the whole loop of a small LP in one workgroup
 // ----------------------------------------------------------------------------
 
@@ -291,12 +517,7 @@ __device__ __forceinline__ void small_sum(double (&v)[NV], double (*sh)[kCheckSu
 {
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        double a = v[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-        v[i] = a;
-    }
+    for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
     if (lane == 0) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) sh[wave][i] = v[i];
@@ -319,12 +540,7 @@ __device__ __forceinline__ void small_sum_once(double (&v)[NV], double (*sh)[kCh
 {
     const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        double a = v[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off);
-        v[i] = a;
-    }
+    for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
     if (lane == 0) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) sh[wave][i] = v[i];
@@ -855,10 +1071,10 @@ __global__ __launch_bounds__(kBlock) void k_gather_probe(const int *__restrict__
     out[(size_t)blockIdx.x * kBlock + threadIdx.x] = acc;
 }
 
-template <typename T, bool LONG, bool SPLIT>
+template <typename T, bool LONG, bool SPLIT, int U = kStreamNB / kBlock>
 __global__ __launch_bounds__(kBlock) void k_partial_plain(Sliced<T> P, const T *__restrict__ x)
 {
-    sliced_partial<LONG, SPLIT>(P, x);
+    sliced_partial<LONG, SPLIT, U>(P, x);
 }
 
 template <typename T, bool LONG>
@@ -1267,6 +1483,20 @@ hipError_t launch_gather_probe(const int *idx, const T *x, int64_t per_slice, in
     return hipGetLastError();
 }
 
+// the entries per thread of a row block of at most nb nonzeros
+static inline int block_u(int nb) { return nb <= 2 * kBlock ? 2 : nb <= 4 * kBlock ? 4 : 8; }
+
+template <typename T, bool SPLIT>
+static void launch_partial_plain(const Sliced<T> &P, const T *in, hipStream_t s)
+{
+    const dim3 g(P.grid), t(kBlock);
+    switch (block_u(P.nb)) {
+    case 2: hipLaunchKernelGGL((k_partial_plain<T, false, SPLIT, 2>), g, t, 0, s, P, in); break;
+    case 4: hipLaunchKernelGGL((k_partial_plain<T, false, SPLIT, 4>), g, t, 0, s, P, in); break;
+    default: hipLaunchKernelGGL((k_partial_plain<T, false, SPLIT>), g, t, 0, s, P, in); break;
+    }
+}
+
 template <typename T>
 hipError_t launch_spmv(const Sliced<T> &P, const T *in, T *out, hipStream_t s)
 {
@@ -1275,11 +1505,59 @@ hipError_t launch_spmv(const Sliced<T> &P, const T *in, T *out, hipStream_t s)
         if (P.split) hipLaunchKernelGGL((k_partial_plain<T, true, true>), dim3(P.grid), dim3(kBlock), 0, s, P, in);
         else hipLaunchKernelGGL((k_partial_plain<T, true, false>), dim3(P.grid), dim3(kBlock), 0, s, P, in);
         hipLaunchKernelGGL((k_sum_slices<T, true>), dim3(blocks_for(P.rows)), dim3(kBlock), 0, s, P, out);
-    } else {
-        if (P.split) hipLaunchKernelGGL((k_partial_plain<T, false, true>), dim3(P.grid), dim3(kBlock), 0, s, P, in);
-        else hipLaunchKernelGGL((k_partial_plain<T, false, false>), dim3(P.grid), dim3(kBlock), 0, s, P, in);
-        hipLaunchKernelGGL((k_sum_slices<T, false>), dim3(blocks_for(P.rows)), dim3(kBlock), 0, s, P, out);
+        return hipGetLastError();
     }
+    // one slice: its partial rows are the product (every row is in a block)
+    Sliced<T> q = P;
+    if (P.S == 1) q.part = out;
+    if (P.split) launch_partial_plain<T, true>(q, in, s);
+    else launch_partial_plain<T, false>(q, in, s);
+    if (P.S > 1) hipLaunchKernelGGL((k_sum_slices<T, false>), dim3(blocks_for(P.rows)), dim3(kBlock), 0, s, P, out);
+    return hipGetLastError();
+}
+
+template <typename T, bool SPLIT>
+static void launch_fused_dual_t(const Dev<T> &d, const Geo &g, Ctl *ctl, hipStream_t s)
+{
+    const dim3 grid(g.grid_K + 1), t(kBlock);
+    switch (block_u(d.K.nb)) {
+    case 2: hipLaunchKernelGGL((k_fused_dual<T, 2, SPLIT>), grid, t, 0, s, d, ctl); break;
+    case 4: hipLaunchKernelGGL((k_fused_dual<T, 4, SPLIT>), grid, t, 0, s, d, ctl); break;
+    default: hipLaunchKernelGGL((k_fused_dual<T, 8, SPLIT>), grid, t, 0, s, d, ctl); break;
+    }
+}
+
+template <typename T>
+hipError_t launch_fused_dual(const Dev<T> &d, const Geo &g, Ctl *ctl, hipStream_t s)
+{
+    if (d.K.split) launch_fused_dual_t<T, true>(d, g, ctl, s);
+    else launch_fused_dual_t<T, false>(d, g, ctl, s);
+    return hipGetLastError();
+}
+
+template <typename T, bool SPLIT>
+static void launch_fused_update_t(const Dev<T> &d, const Geo &g, const Ctl *in, const double *pin, Ctl *out, hipStream_t s)
+{
+    const dim3 grid(g.grid), t(kBlock);
+    switch (block_u(d.KT.nb)) {
+    case 2: hipLaunchKernelGGL((k_fused_update<T, 2, SPLIT>), grid, t, 0, s, d, in, pin, out, g.grid_K, g.vb_m); break;
+    case 4: hipLaunchKernelGGL((k_fused_update<T, 4, SPLIT>), grid, t, 0, s, d, in, pin, out, g.grid_K, g.vb_m); break;
+    default: hipLaunchKernelGGL((k_fused_update<T, 8, SPLIT>), grid, t, 0, s, d, in, pin, out, g.grid_K, g.vb_m); break;
+    }
+}
+
+template <typename T>
+hipError_t launch_fused_update(const Dev<T> &d, const Geo &g, const Ctl *in, const double *part_in, Ctl *out,
+                               hipStream_t s)
+{
+    if (d.KT.split) launch_fused_update_t<T, true>(d, g, in, part_in, out, s);
+    else launch_fused_update_t<T, false>(d, g, in, part_in, out, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_ctl(const Ctl *in, const double *part_in, Ctl *out, double *part_out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_copy_ctl, dim3(1), dim3(kBlock), 0, s, in, part_in, out, part_out);
     return hipGetLastError();
 }
 
@@ -1450,6 +1728,9 @@ hipError_t scale_csr_pair(const int *rp, const int *ci, double *kv, int m, const
 }
 
 #define PDLP_INSTANTIATE(T)                                                                                        \
+    template hipError_t launch_fused_dual<T>(const Dev<T> &, const Geo &, Ctl *, hipStream_t);                     \
+    template hipError_t launch_fused_update<T>(const Dev<T> &, const Geo &, const Ctl *, const double *, Ctl *,       \
+                                                   hipStream_t);                                                   \
     template hipError_t launch_partial_K<T>(const Dev<T> &, hipStream_t);                                          \
     template hipError_t launch_partial_KT<T>(const Dev<T> &, hipStream_t);                                         \
     template hipError_t launch_dual<T>(const Dev<T> &, const Geo &, hipStream_t);                                  \
