@@ -76,6 +76,11 @@ struct lp_batch {
     int shape[2][2] = {{kStreamNB, kStreamRB}, {kStreamNB, kStreamRB}};   // K, K': most nonzeros, rows per block
     double seconds = 0;
     std::string err;
+    // Points of the last solve on the host, of instances [ahead_lo, ahead_hi):
+    // fetched together when results are read in order (do_batch_result)
+    std::vector<double> ahead_x, ahead_y, ahead_lam;
+    int ahead_lo = 0, ahead_hi = 0;
+    int ahead_count = 0, ahead_next = 0;   // instances of the last fetch; the one after it
 
     template <typename T> BDev<T> &dev();
     ~lp_batch()
@@ -719,6 +724,7 @@ int do_batch_solve(lp_batch *P, double tol, int64_t max_iters, double time_limit
     const int64_t N = P->Ntot, M = P->Mtot;
     auto t0 = std::chrono::steady_clock::now();
     auto elapsed = [&] { return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count(); };
+    P->ahead_lo = P->ahead_hi = P->ahead_count = P->ahead_next = 0;   // the points fetched ahead were the last solve's
     // a solve starts with every instance's chunks and blocks in the lists
     // (the start products below need all of them)
     const bool narrowed = P->active >= 0;
@@ -880,21 +886,69 @@ int do_batch_solve(lp_batch *P, double tol, int64_t max_iters, double time_limit
     return LP_OK;
 }
 
+// The points of instances [i, i + count), unscaled, to the staging vectors
+// (from their start)
+template <typename T>
+void unscale_points(lp_batch *P, int i, int count)
+{
+    Dev<T> v = view_of<T>(P, i);
+    v.n = (int)(P->noff[i + count] - P->noff[i]);
+    v.m = (int)(P->moff[i + count] - P->moff[i]);
+    HIPT(launch_result<T>(v, P->stage_n0, P->stage_m, P->stage_n1, P->stream));
+}
+
+// Most values of one fetch of several instances' points
+constexpr int64_t kAheadValues = (int64_t)4 << 17;   // 4 MiB of doubles
+
+// The point of instance i.  A program that reads every instance's result asks
+// for them one after another, and each used to cost a launch over the whole
+// batch, three copies and a wait (256 LPs of 300 to 1000 columns: 17 of the
+// 20 ms that their solve and results took).  Read in order, they come in
+// fetches of 1, 2, 4, ... instances up to 4 MiB; out of order, one by one.
+template <typename T>
+void batch_point(lp_batch *P, int i, double *x, double *y, double *lam)
+{
+    hipStream_t st = P->stream;
+    if (i < P->ahead_lo || i >= P->ahead_hi) {
+        int count = i > 0 && i == P->ahead_next ? 2 * P->ahead_count : 1;
+        count = std::min(count, P->B - i);
+        auto values = [&](int k) { return 2 * (P->noff[i + k] - P->noff[i]) + P->moff[i + k] - P->moff[i]; };
+        while (count > 1 && values(count) > kAheadValues) --count;
+        P->ahead_lo = P->ahead_hi = 0;
+        P->ahead_count = count;
+        P->ahead_next = i + count;
+        unscale_points<T>(P, i, count);
+        if (count == 1) {
+            if (x) d2h(st, x, (const double *)P->stage_n0, P->n[i]);
+            if (lam) d2h(st, lam, (const double *)P->stage_n1, P->n[i]);
+            if (y) d2h(st, y, (const double *)P->stage_m, P->m[i]);
+            bsync(P);
+            return;
+        }
+        const int64_t n = P->noff[i + count] - P->noff[i], m = P->moff[i + count] - P->moff[i];
+        P->ahead_x.resize((size_t)n);
+        P->ahead_lam.resize((size_t)n);
+        P->ahead_y.resize((size_t)m);
+        d2h(st, P->ahead_x.data(), (const double *)P->stage_n0, n);
+        d2h(st, P->ahead_lam.data(), (const double *)P->stage_n1, n);
+        d2h(st, P->ahead_y.data(), (const double *)P->stage_m, m);
+        bsync(P);
+        P->ahead_lo = i;
+        P->ahead_hi = i + count;
+    }
+    const int64_t n0 = P->noff[i] - P->noff[P->ahead_lo], m0 = P->moff[i] - P->moff[P->ahead_lo];
+    if (x) std::copy_n(P->ahead_x.begin() + n0, P->n[i], x);
+    if (lam) std::copy_n(P->ahead_lam.begin() + n0, P->n[i], lam);
+    if (y) std::copy_n(P->ahead_y.begin() + m0, P->m[i], y);
+}
+
 template <typename T>
 int do_batch_result(lp_batch *P, int i, double *x, double *y, double *lam, lp_info *info)
 {
-    BDev<T> &b = P->dev<T>();
-    if (x || y || lam) {
-        HIPT(launch_result<T>(b.d, P->stage_n0, P->stage_m, P->stage_n1, P->stream));
-        if (x) d2h(P->stream, x, (const double *)P->stage_n0 + P->noff[i], P->n[i]);
-        if (lam) d2h(P->stream, lam, (const double *)P->stage_n1 + P->noff[i], P->n[i]);
-        if (y) d2h(P->stream, y, (const double *)P->stage_m + P->moff[i], P->m[i]);
-        bsync(P);
-    }
+    if (x || y || lam) batch_point<T>(P, i, x, y, lam);
     if (info) {
-        Ctl c;
-        HIPT(hipMemcpyAsync(&c, b.ctl + i, sizeof(Ctl), hipMemcpyDeviceToHost, P->stream));
-        bsync(P);
+        // the host's copy: every solve ends, and every state is set, with it current
+        const Ctl &c = P->hctl[i];
         info->status = c.status;
         info->pobj = c.out_pobj;
         info->dobj = c.out_dobj;
@@ -1056,6 +1110,8 @@ int lp_batch_result(const lp_batch *Pc, int32_t i, double *x, double *y, double 
                         : do_batch_result<double>(P, i, x, y, lambda, info);
     } catch (const HipError &h) {
         return fail(P, h);
+    } catch (const std::bad_alloc &) {
+        return LP_ERR_NOMEM;
     }
 }
 

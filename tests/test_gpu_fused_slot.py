@@ -36,9 +36,7 @@ CASES = [
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("name,make,opt", CASES, ids=[c[0] for c in CASES])
-def test_fused_slot_matches_oracle(name, make, opt, precision):
-    from paper_2312_14832_amd import lp as lpmod
-    from oracle import oracle as oracle_mod
+def test_fused_slot_matches_oracle(lpmod, oracle_mod, name, make, opt, precision):
     say(f"case fused slot {name} {precision}")
     data = make()
     # FP32: 8 steps, each within the single step's 64 u normwise and growing
