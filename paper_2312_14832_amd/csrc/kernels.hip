@@ -566,16 +566,15 @@ __device__ __noinline__ void small_check_decision(Ctl *c, const double *S, const
     check_decision(c, S, R, Nq, Nc);
 }
 
-// row r of a plain CSR (rp, ci, v) against x, entries in order; eight at a
+// entries [b, e) of a plain CSR's row (ci, v) against x, in order; eight at a
 // time in straight-line phases so their loads overlap (slots past the row's
 // end re-read its last entry and are masked out of the sum)
 template <typename T, int U = 8>
-__device__ __forceinline__ T small_row(const int *__restrict__ rp, const int *__restrict__ ci,
-                                       const T *__restrict__ v, const T *__restrict__ x, int r)
+__device__ __forceinline__ T small_row(int b, int e, const int *__restrict__ ci, const T *__restrict__ v,
+                                       const T *__restrict__ x)
 {
-    const int e = rp[r + 1];
     T acc = T(0);
-    for (int p = rp[r]; p < e; p += U) {
+    for (int p = b; p < e; p += U) {
         int c[U];
         T a[U], g[U];
 #pragma unroll
@@ -660,7 +659,7 @@ __global__ __launch_bounds__(kSmall) void k_small_loop(Dev<T> d, int max_slots, 
             double v[3] = {dx2, 0.0, 0.0};
             for (int i = tid; i < d.m; i += kSmall) {
                 const T yo = y[i], ko = kx[i], qi = d.qs[i];
-                const T s = small_row(krp, kci, kv, xg, i);
+                const T s = small_row(krp[i], krp[i + 1], kci, kv, xg);
                 T val = yo + sigma * (qi - T(2) * s + ko);
                 if (i >= d.m1 && val < T(0)) val = T(0);
                 yn[i] = val;
@@ -698,7 +697,7 @@ __global__ __launch_bounds__(kSmall) void k_small_loop(Dev<T> d, int max_slots, 
                 const bool primal = sc.mode == MODE_NONE;
                 for (int j = tid; j < d.n; j += kSmall) {
                     const T xj = x[j], a = d.xa[j], b = d.KTya[j];
-                    const T s = small_row(trp, tci, tv, yg, j);
+                    const T s = small_row(trp[j], trp[j + 1], tci, tv, yg);
                     kty[j] = s;
                     d.xa[j] = a + w * (xj - a);
                     d.KTya[j] = b + w * (s - b);
@@ -767,14 +766,20 @@ __global__ __launch_bounds__(kSmall) void k_small_loop(Dev<T> d, int max_slots, 
 // apply_row.  The step rule's two factors for the accepted counts this
 // launch can reach (at most max_slots of them) are tabulated in LDS at
 // entry, so the per-slot step decision is plain arithmetic, which every
-// thread takes for itself while thread 0 alone updates the controller.
+// thread takes for itself (one thread updating the controller beside it took
+// the decision's four divisions a second time, and its wavefront with it).
+// At 1000 columns, 500 rows and 5000 nonzeros a slot takes 3.8 us (with
+// wave_sum and without that 4.3), most of it instruction issue and LDS round
+// trips of the one workgroup's two wavefronts a SIMD.  Entries laid out by
+// their place in the row, rows sorted by length (3.7 us, but 60 us to sort) and
+// eight entries at a time instead of four (4.1) were no better.
 // kSmallReg threads (fewer than the other forms) leave each thread enough
 // registers to hold its R columns and rows without spilling.  The body is
 // shared by the single-LP kernel and the batched one (a workgroup per LP).
 template <typename T, int R>
 __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, double Nq, double Nc)
 {
-    constexpr int NT = kSmallReg;
+    constexpr int NT = kSmallReg, U = 4;
     extern __shared__ double dyn[];
     __shared__ Ctl sc;
     __shared__ double sh[NT / 64][kCheckSums];
@@ -797,12 +802,16 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
     if (tid == 0) sc = *d.ctl;
     __syncthreads();
     const long long k0 = sc.k;
-    const int sc_fixed = sc.fixed_step, sc_every = sc.check_every;   // fixed for the launch
-    const long long sc_maxit = sc.max_iters;
-    for (int t = tid; t < max_slots; t += NT) step_factors(k0 + t, tab[2 * t], tab[2 * t + 1]);
-    // columns j = tid + r NT, rows i = tid + r NT
+    const int fixed = sc.fixed_step, every = sc.check_every;   // fixed for the launch
+    const long long max_iters = sc.max_iters;
+    // the accepted counts this launch can reach: a step a slot, and none at
+    // the iteration limit
+    const int reach = (int)min((long long)max_slots, max(max_iters - k0, 0LL) + 1);
+    for (int t = tid; t < reach; t += NT) step_factors(k0 + t, tab[2 * t], tab[2 * t + 1]);
+    // columns j = tid + r NT, rows i = tid + r NT, and the extents of their entries
     T xc[R], xt[R], ktc[R], xa[R], kta[R], cj[R], lj[R], uj[R];
     T yc[R], kxc[R], ya[R], kxa[R], qi[R], yt[R], kxt[R];
+    int kb[R], ke[R], tb[R], te[R];
     double dx2 = 0.0;
     {
         const int c = sc.cur;
@@ -811,12 +820,14 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
             const int j = tid + r * NT, i = j;
             xc[r] = xt[r] = ktc[r] = xa[r] = kta[r] = cj[r] = lj[r] = uj[r] = T(0);
             yc[r] = kxc[r] = ya[r] = kxa[r] = qi[r] = yt[r] = kxt[r] = T(0);
+            kb[r] = ke[r] = tb[r] = te[r] = 0;
             if (j < d.n) {
                 xc[r] = pick(d.xb, c)[j];
                 xt[r] = pick(d.xb, c ^ 1)[j];
                 ktc[r] = pick(d.KTyb, c)[j];
                 xa[r] = d.xa[j]; kta[r] = d.KTya[j];
                 cj[r] = d.cs[j]; lj[r] = d.ls[j]; uj[r] = d.us[j];
+                tb[r] = strp[j]; te[r] = strp[j + 1];
                 sx[j] = xt[r];
                 const double dd = (double)xt[r] - (double)xc[r];
                 dx2 += dd * dd;
@@ -826,18 +837,36 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
                 kxc[r] = pick(d.Kxb, c)[i];
                 ya[r] = d.ya[i]; kxa[r] = d.Kxa[i];
                 qi[r] = d.qs[i];
+                kb[r] = skrp[i]; ke[r] = skrp[i + 1];
             }
         }
     }
     __syncthreads();
-    for (int slot = 0; slot < max_slots; ++slot) {
-        if (sc.done) break;   // the same LDS value for every thread
-        // the controller fields the step decision reads, taken before the
-        // barrier after which thread 0 updates the controller
-        const double eta = sc.eta, omega = sc.omega, W = sc.W;
-        const long long kk = sc.k;
-        int accepted, mode;
-        double eta_next, avg_w = 0.0;
+    // What the slots change of the controller, in every thread's registers:
+    // each takes the step decision for itself, with the same arithmetic on the
+    // same values.  Thread 0 puts them back for a check and at the end, and
+    // every thread reads what a check decided.
+    double eta = sc.eta, omega = sc.omega, W = sc.W, eta_last = sc.eta_last, avg_w = sc.avg_w;
+    int at = 0, steps = 0, tries = 0;   // since the launch began: k - k0; since the last put back: accepted, attempted
+    int cur = sc.cur, mode = sc.mode, accepted = sc.accepted, numerical = 0;
+    auto put_back = [&] {
+        if (tid == 0) {
+            sc.eta = eta;
+            sc.W = W;
+            sc.avg_w = avg_w;
+            sc.eta_last = eta_last;
+            sc.k = k0 + at;
+            sc.t += steps;
+            sc.attempts += tries;
+            sc.cur = cur;
+            sc.mode = mode;
+            sc.accepted = accepted;
+            if (numerical) sc.numerical = 1;
+        }
+        steps = tries = 0;
+    };
+    bool done = sc.done;
+    for (int slot = 0; slot < max_slots && !done; ++slot) {
         {
             // K x' and the dual step
             const T sigma = (T)(eta * omega);
@@ -846,7 +875,7 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
             for (int r = 0; r < R; ++r) {
                 const int i = tid + r * NT;
                 if (i < d.m) {
-                    const T s = small_row<T, 4>(skrp, skci, skv, (const T *)sx, i);
+                    const T s = small_row<T, U>(kb[r], ke[r], skci, skv, (const T *)sx);
                     T val = yc[r] + sigma * (qi[r] - T(2) * s + kxc[r]);
                     if (i >= d.m1 && val < T(0)) val = T(0);
                     yt[r] = val;
@@ -858,19 +887,26 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
                 }
             }
             small_sum_once<3, NT>(v, sh);
-            // every thread takes the step decision (the same arithmetic as
-            // thread 0's update of the controller, so no barrier is needed
-            // before the results are used)
-            const int at = (int)(kk - k0);   // < max_slots: one accepted step per slot at most
-            const int rule = step_rule(eta, omega, sc_fixed, v[0], v[1], v[2], tab[2 * at], tab[2 * at + 1], eta_next);
+            double eta_next;
+            const int rule = step_rule(eta, omega, fixed, v[0], v[1], v[2], tab[2 * at], tab[2 * at + 1], eta_next);
+            ++tries;
             accepted = rule == 1;
-            mode = rule < 0 ? MODE_CHECK : (rule == 1 ? mode_after_accept(kk + 1, sc_every, sc_maxit) : MODE_NONE);
-            if (rule < 0) eta_next = eta;
-            if (rule == 1) avg_w = eta / (W + eta);
-            if (tid == 0) step_decision_f(&sc, v[0], v[1], v[2], tab[2 * at], tab[2 * at + 1]);
+            if (rule == 1) {
+                W += eta;
+                avg_w = eta / W;
+                eta_last = eta;
+                ++at;
+                ++steps;
+                cur ^= 1;
+                mode = mode_after_accept(k0 + at, every, max_iters);
+            } else {
+                mode = rule < 0 ? MODE_CHECK : MODE_NONE;
+                numerical |= rule < 0;
+            }
+            if (rule >= 0) eta = eta_next;
         }
         {
-            const T tau = (T)(eta_next / omega);
+            const T tau = (T)(eta / omega);
             dx2 = 0.0;
             if (!accepted) {
 #pragma unroll
@@ -899,7 +935,7 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
                     }
                     if (j < d.n) {
                         xc[r] = xt[r];
-                        const T s = small_row<T, 4>(strp, stci, stv, (const T *)sy, j);
+                        const T s = small_row<T, U>(tb[r], te[r], stci, stv, (const T *)sy);
                         ktc[r] = s;
                         xa[r] = xa[r] + w * (xc[r] - xa[r]);
                         kta[r] = kta[r] + w * (s - kta[r]);
@@ -913,9 +949,10 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
                     }
                 }
             }
+            if (mode != MODE_NONE) put_back();
             __syncthreads();
         }
-        if (sc.mode != MODE_NONE) {
+        if (mode != MODE_NONE) {   // the same for every thread
             double cs[kCheckSums], rs[kRaySums];
 #pragma unroll
             for (int k = 0; k < kCheckSums; ++k) cs[k] = 0.0;
@@ -946,7 +983,10 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
             if (tid == 0) small_check_decision(&sc, cs, rs, Nq, Nc);
             __syncthreads();
             const int rt = sc.restart_to, co = sc.copy_out, sel = sc.out_sel, np = sc.need_primal;
-            const T tau = (T)(sc.eta / sc.omega);
+            omega = sc.omega;
+            W = sc.W;
+            done = sc.done;
+            const T tau = (T)(eta / omega);
             dx2 = 0.0;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -999,7 +1039,9 @@ __device__ __forceinline__ void small_reg_body(const Dev<T> &d, int max_slots, d
         }
     }
     // back to the buffers of the multi-kernel path
-    const int c = sc.cur;
+    put_back();
+    __syncthreads();
+    const int c = cur;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = tid + r * NT, j = i;
