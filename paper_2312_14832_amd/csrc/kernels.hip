@@ -768,11 +768,12 @@ __global__ __launch_bounds__(kSmall) void k_small_loop(Dev<T> d, int max_slots, 
 // entry, so the per-slot step decision is plain arithmetic, which every
 // thread takes for itself (one thread updating the controller beside it took
 // the decision's four divisions a second time, and its wavefront with it).
-// At 1000 columns, 500 rows and 5000 nonzeros a slot takes 3.8 us (with
-// wave_sum and without that 4.3), most of it instruction issue and LDS round
-// trips of the one workgroup's two wavefronts a SIMD.  Entries laid out by
-// their place in the row, rows sorted by length (3.7 us, but 60 us to sort) and
-// eight entries at a time instead of four (4.1) were no better.
+// At 1000 columns, 500 rows and 5000 nonzeros a slot takes 3.81 us (3.91 with
+// the controller in LDS, 4.34 with that and sums over shuffles), at half of
+// each 2.93 (3.11, 3.44), launch and set-up apart.  The one workgroup's issue
+// bounds it: eight entries of a row at a time, masked past its end, take 4.05
+// and 3.30, and rows sorted by length, their entries laid out by place, 3.64
+// and 2.68, but some 60 us at 1000 columns to sort at entry.
 // kSmallReg threads (fewer than the other forms) leave each thread enough
 // registers to hold its R columns and rows without spilling.  The body is
 // shared by the single-LP kernel and the batched one (a workgroup per LP).
