@@ -196,25 +196,25 @@ struct BDev {
 };
 
 // Batched solves of one family: every instance shares the matrix K (pattern
-// and values) and has its own c, q, l, u.  Vectors are interleaved, [row][Bp]
-// with the instance fastest (Bp = the instance count rounded up to a power
-// of two, at most kBlock; padded instances are inert and finished from the
-// start), so a product reads K once for every instance and each gather of
-// x[j][0..Bp) is a contiguous run.  d holds the interleaved vectors with
-// d.n = n Bp, d.m = m Bp, d.m1 = m1 Bp and the scaling factors replicated per
-// instance, so the element functions of the single-LP path apply unchanged
-// with element e = row * Bp + instance.
+// and values) and has its own c, q, l, u.  The instances are in G groups of W,
+// padded ones inert and finished from the start, and vectors are interleaved
+// by group, [group][row][W] with the instance fastest, so a product reads K
+// once for a group and each gather of x[j][0..W) is a contiguous run.  d holds
+// the interleaved vectors with d.n = n G W, d.m = m G W and the scaling factors
+// replicated per instance, so the element functions of the single-LP path
+// apply unchanged to an element (d.m1 does not: see m1).
 template <typename T>
 struct SDev {
     Dev<T> d;
-    int B, Bp, lgB;           // instances, padded count, log2(Bp)
-    int n, m;                 // columns and rows of K (per instance)
+    int B, Bp, G, lgW;        // instances, padded count, groups, log2 of a group's width (Bp = G << lgW)
+    int over_G;               // 2^16 / G + 1
+    int n, m, m1;             // columns, rows and equality rows of K (per instance)
     const int *krp, *kci;     // K~  (m x n) CSR, shared
     const T *kv;
     const int *trp, *tci;     // K~' (n x m) CSR, shared
     const T *tv;
     int grid;                 // workgroups of the update / check / apply walks (the same walk in each)
-    int grid_m;               // workgroups of the dual kernel
+    int grid_m;               // workgroups of the dual kernel (multiples of kXcds, both)
     const double *Nq, *Nc;    // [Bp] |q|, |c| of each instance's unscaled data
     Ctl *ctl;                 // [Bp]
     int *gate;                // 1 while some instance is in a check this slot
@@ -228,10 +228,13 @@ template <typename T> hipError_t launch_shared_apply(const SDev<T> &S, hipStream
 template <typename T> hipError_t launch_shared_product(const SDev<T> &S, int which, const T *in, T *out,
                                                        hipStream_t s);
 // instance b of an interleaved vector of `rows` rows to / from a plain FP64 vector
-template <typename T> hipError_t launch_shared_extract(const T *src, int lgB, int b, double *dst, int rows,
+template <typename T> hipError_t launch_shared_extract(const T *src, int lgW, int b, double *dst, int rows,
                                                        hipStream_t s);
-template <typename T> hipError_t launch_shared_insert(const double *src, int lgB, int b, T *dst, int rows,
+template <typename T> hipError_t launch_shared_insert(const double *src, int lgW, int b, T *dst, int rows,
                                                       hipStream_t s);
+// the start of every instance: proj_X(xs), proj_Y(ys) in buffer 0 (unscaled, interleaved; nullptr: zero)
+template <typename T> hipError_t launch_shared_start(const SDev<T> &S, const double *xs, const double *ys,
+                                                     hipStream_t s);
 hipError_t launch_shared_set_final(Ctl *ctl, int Bp, int status, hipStream_t s);
 
 template <typename T> hipError_t launch_batch_product(const BDev<T> &b, int which, hipStream_t s);

@@ -27,7 +27,7 @@ constexpr int kMaxShared = kBlock;   // instances per handle (the interleave wid
 }  // namespace
 
 struct lp_shared {
-    int B = 0, Bp = 1, lgB = 0;
+    int B = 0, Bp = 1, G = 1, lgW = 0;
     int64_t n = 0, m = 0, m1 = 0, nnz = 0;
     lp_options opt{};
     hipStream_t stream = nullptr;
@@ -60,6 +60,11 @@ struct lp_shared {
     std::string err;
 
     template <typename T> SDev<T> &dev();
+    // element of instance b's row r in an interleaved vector of `rows` rows
+    int64_t at(int64_t rows, int64_t r, int b) const
+    {
+        return (((b >> lgW) * rows + r) << lgW) + (b & ((1 << lgW) - 1));
+    }
     ~lp_shared()
     {
         if (graph) (void)hipGraphExecDestroy(graph);
@@ -119,12 +124,14 @@ void setup(lp_shared *P, const std::vector<int> &rp, const std::vector<int> &ci,
     const int64_t N = P->n * P->Bp, M = P->m * P->Bp, nnz = P->nnz;
     S.B = P->B;
     S.Bp = P->Bp;
-    S.lgB = P->lgB;
+    S.G = P->G;
+    S.over_G = 65536 / P->G + 1;
+    S.lgW = P->lgW;
     S.n = (int)P->n;
     S.m = (int)P->m;
+    S.m1 = (int)P->m1;
     d.n = (int)N;
     d.m = (int)M;
-    d.m1 = (int)(P->m1 * P->Bp);
     d.Dr = Drr;
     d.Dc = Dcr;
     int *krp = A.make<int>(P->m + 1), *kci = A.make<int>(nnz), *trp = A.make<int>(P->n + 1), *tci = A.make<int>(nnz);
@@ -158,11 +165,14 @@ void setup(lp_shared *P, const std::vector<int> &rp, const std::vector<int> &ci,
         HIPT(hipMemsetAsync(p, 0, sizeof(T) * (size_t)std::max<int64_t>(N, 1), st));
     for (T *p : {d.yb[0], d.yb[1], d.Kxb[0], d.Kxb[1], d.ya, d.Kxa, d.y0, d.Kx0, d.yo})
         HIPT(hipMemsetAsync(p, 0, sizeof(T) * (size_t)std::max<int64_t>(M, 1), st));
-    // the element walks: enough workgroups to cover the longer side, at most
-    // 2048 (eight 256-thread workgroups per CU)
-    const int64_t wn = (std::max(N, M) + kBlock - 1) / kBlock;
-    S.grid = (int)std::max<int64_t>(1, std::min<int64_t>(wn, 2048));
-    S.grid_m = (int)std::max<int64_t>(1, std::min<int64_t>((M + kBlock - 1) / kBlock, 2048));
+    // the element walks: enough workgroups on each XCD to cover its share of
+    // the longer side, at most 256 (eight 256-thread workgroups per CU)
+    auto walk_grid = [&](int64_t rows) {
+        const int64_t tiles = ((rows << P->lgW) + kBlock - 1) / kBlock * P->G;
+        return kXcds * (int)std::max<int64_t>(1, std::min<int64_t>((tiles + kXcds - 1) / kXcds, 256));
+    };
+    S.grid = walk_grid(std::max(P->n, P->m));
+    S.grid_m = walk_grid(P->m);
     d.part_primal = A.make<double>((int64_t)S.grid * S.Bp);
     d.part_dual = A.make<double>((int64_t)S.grid_m * S.Bp * 2);
     d.part_check = A.make<double>((int64_t)S.grid * S.Bp * kCheckSums);
@@ -197,11 +207,11 @@ int do_load(lp_shared *P, const lp_csr *K, const double *const *c, const double 
     std::vector<double> hc(N, 0.0), hl(N, 0.0), hu(N, 0.0), hq(M, 0.0);
     for (int b = 0; b < B; ++b) {
         for (int64_t j = 0; j < n; ++j) {
-            hc[j * Bp + b] = c[b][j];
-            hl[j * Bp + b] = l[b][j];
-            hu[j * Bp + b] = u[b][j];
+            hc[P->at(n, j, b)] = c[b][j];
+            hl[P->at(n, j, b)] = l[b][j];
+            hu[P->at(n, j, b)] = u[b][j];
         }
-        for (int64_t i = 0; i < m; ++i) hq[i * Bp + b] = q[b][i];
+        for (int64_t i = 0; i < m; ++i) hq[P->at(m, i, b)] = q[b][i];
     }
     // unscaled norms per instance
     P->Nq.assign(Bp, 0.0);
@@ -245,9 +255,9 @@ int do_load(lp_shared *P, const lp_csr *K, const double *const *c, const double 
     // the factors replicated per instance, the scaled interleaved vectors
     std::vector<double> hDr(M), hDc(N);
     for (int64_t i = 0; i < m; ++i)
-        for (int b = 0; b < Bp; ++b) hDr[i * Bp + b] = P->Dr[i];
+        for (int b = 0; b < Bp; ++b) hDr[P->at(m, i, b)] = P->Dr[i];
     for (int64_t j = 0; j < n; ++j)
-        for (int b = 0; b < Bp; ++b) hDc[j * Bp + b] = P->Dc[j];
+        for (int b = 0; b < Bp; ++b) hDc[P->at(n, j, b)] = P->Dc[j];
     double *Drr = A.make<double>(M), *Dcr = A.make<double>(N);
     double *d_c = A.make<double>(N), *d_l = A.make<double>(N), *d_u = A.make<double>(N), *d_q = A.make<double>(M);
     double *cs = A.make<double>(N), *ls = A.make<double>(N), *us = A.make<double>(N), *qs = A.make<double>(M);
@@ -361,16 +371,16 @@ void resolve_shared_confirms(lp_shared *P)
         any = true;
         conf[(size_t)b] = 1;
         const int cur = c.cur;
-        HIPT(launch_shared_extract<T>(d.xb[cur], S.lgB, b, v[0], n, st));
-        HIPT(launch_shared_extract<T>(d.xa, S.lgB, b, v[1], n, st));
-        HIPT(launch_shared_extract<T>(d.x0, S.lgB, b, v[2], n, st));
-        HIPT(launch_shared_extract<double>(P->cs64, S.lgB, b, v[3], n, st));
-        HIPT(launch_shared_extract<double>(P->ls64, S.lgB, b, v[4], n, st));
-        HIPT(launch_shared_extract<double>(P->us64, S.lgB, b, v[5], n, st));
-        HIPT(launch_shared_extract<T>(d.yb[cur], S.lgB, b, v[6], m, st));
-        HIPT(launch_shared_extract<T>(d.ya, S.lgB, b, v[7], m, st));
-        HIPT(launch_shared_extract<T>(d.y0, S.lgB, b, v[8], m, st));
-        HIPT(launch_shared_extract<double>(P->qs64, S.lgB, b, v[9], m, st));
+        HIPT(launch_shared_extract<T>(d.xb[cur], S.lgW, b, v[0], n, st));
+        HIPT(launch_shared_extract<T>(d.xa, S.lgW, b, v[1], n, st));
+        HIPT(launch_shared_extract<T>(d.x0, S.lgW, b, v[2], n, st));
+        HIPT(launch_shared_extract<double>(P->cs64, S.lgW, b, v[3], n, st));
+        HIPT(launch_shared_extract<double>(P->ls64, S.lgW, b, v[4], n, st));
+        HIPT(launch_shared_extract<double>(P->us64, S.lgW, b, v[5], n, st));
+        HIPT(launch_shared_extract<T>(d.yb[cur], S.lgW, b, v[6], m, st));
+        HIPT(launch_shared_extract<T>(d.ya, S.lgW, b, v[7], m, st));
+        HIPT(launch_shared_extract<T>(d.y0, S.lgW, b, v[8], m, st));
+        HIPT(launch_shared_extract<double>(P->qs64, S.lgW, b, v[9], m, st));
         Dev<double> w{};   // member b as a plain FP64 LP (only what the re-check reads)
         w.m = m;
         w.n = n;
@@ -427,7 +437,7 @@ int do_solve(lp_shared *P, double tol, int64_t max_iters, double time_limit)
         // start: x = proj_X(start or 0), y = proj_Y(start or 0), per instance
         bool any_start = false;
         for (int b = 0; b < B; ++b) any_start = any_start || P->has_start[b];
-        HIPT(launch_start<T>(d, any_start ? P->start_x : nullptr, any_start ? P->start_y : nullptr, 0, st));
+        HIPT(launch_shared_start<T>(S, any_start ? P->start_x : nullptr, any_start ? P->start_y : nullptr, st));
         for (int b = 0; b < Bp; ++b) {
             Ctl c{};
             if (b < B) {
@@ -550,17 +560,17 @@ int do_result(lp_shared *P, int i, double *x, double *y, double *lam, lp_info *i
         }
         const int n = (int)P->n, m = (int)P->m;
         if (x) {
-            HIPT(launch_shared_extract<double>(P->stage_n0, P->lgB, i, P->pick_n, n, st));
+            HIPT(launch_shared_extract<double>(P->stage_n0, P->lgW, i, P->pick_n, n, st));
             d2h(st, x, (const double *)P->pick_n, n);
             ssync(P);
         }
         if (lam) {
-            HIPT(launch_shared_extract<double>(P->stage_n1, P->lgB, i, P->pick_n, n, st));
+            HIPT(launch_shared_extract<double>(P->stage_n1, P->lgW, i, P->pick_n, n, st));
             d2h(st, lam, (const double *)P->pick_n, n);
             ssync(P);
         }
         if (y) {
-            HIPT(launch_shared_extract<double>(P->stage_m, P->lgB, i, P->pick_m, m, st));
+            HIPT(launch_shared_extract<double>(P->stage_m, P->lgW, i, P->pick_m, m, st));
             d2h(st, y, (const double *)P->pick_m, m);
             ssync(P);
         }
@@ -616,7 +626,7 @@ int do_get_state(lp_shared *P, int i, double *buf)
     for (int k = 0; k < 10; ++k) {
         const int rows = (int)(is_n[k] ? P->n : P->m);
         double *pick = is_n[k] ? P->pick_n : P->pick_m;
-        HIPT(launch_shared_extract<T>(v[k], P->lgB, i, pick, rows, st));
+        HIPT(launch_shared_extract<T>(v[k], P->lgW, i, pick, rows, st));
         d2h(st, p, (const double *)pick, rows);
         ssync(P);
         p += rows;
@@ -642,7 +652,7 @@ int do_set_state(lp_shared *P, int i, const double *buf)
         const int rows = (int)(is_n[k] ? P->n : P->m);
         double *pick = is_n[k] ? P->pick_n : P->pick_m;
         h2d(st, pick, p, rows);
-        HIPT(launch_shared_insert<T>(pick, P->lgB, i, v[k], rows, st));
+        HIPT(launch_shared_insert<T>(pick, P->lgW, i, v[k], rows, st));
         ssync(P);
         p += rows;
     }
@@ -679,13 +689,21 @@ int lp_shared_load(lp_shared **out, int32_t count, const lp_csr *K, const double
         return LP_ERR_ARG;
     std::unique_ptr<lp_shared> P(new lp_shared());
     P->B = count;
-    while (P->Bp < count) {
-        P->Bp <<= 1;
-        ++P->lgB;
-    }
+    int64_t pow2 = 1;
+    while (pow2 < count) pow2 <<= 1;
     // interleaved vectors and element indices stay below 2^30
-    if ((K->n + 1) * P->Bp >= (int64_t(1) << 30) || (K->m + 1) * P->Bp >= (int64_t(1) << 30))
+    if ((K->n + 1) * pow2 >= (int64_t(1) << 30) || (K->m + 1) * pow2 >= (int64_t(1) << 30))
         return LP_ERR_TOO_LARGE;
+    // A group's row of a vector is a cache line: 16 instances in FP64, 32 in
+    // FP32.  Narrower ones read K more often and fetch half lines (64 members,
+    // 1e5 columns, sk_dual and sk_update together: FP64 332 us with 8, 253 with
+    // 16, 256 with 32, 261 with 64; FP32 217, 171, 149 and 153), so FP32 takes
+    // 16 only where that leaves out more than an eighth of the lanes as padding.
+    // All instances are one group, of the next power of two, where fewer.
+    const int full = o.precision == LP_MIXED && (count + 31) / 32 * 28 <= (count + 15) / 16 * 16 ? 32 : 16;
+    while ((1 << P->lgW) < full && (1 << P->lgW) < count) ++P->lgW;
+    P->G = (int)((count + (1 << P->lgW) - 1) >> P->lgW);
+    P->Bp = P->G << P->lgW;
     P->n = K->n;
     P->m = K->m;
     P->m1 = m1;
@@ -726,10 +744,10 @@ int lp_shared_set_start(lp_shared *P, int32_t i, const double *x0, const double 
         // the instance's slice of the interleaved start (zeros where NULL)
         if (x0) h2d(st, P->pick_n, x0, n);
         else if (n) HIPT(hipMemsetAsync(P->pick_n, 0, sizeof(double) * (size_t)n, st));
-        HIPT(launch_shared_insert<double>(P->pick_n, P->lgB, i, P->start_x, n, st));
+        HIPT(launch_shared_insert<double>(P->pick_n, P->lgW, i, P->start_x, n, st));
         if (y0) h2d(st, P->pick_m, y0, m);
         else if (m) HIPT(hipMemsetAsync(P->pick_m, 0, sizeof(double) * (size_t)m, st));
-        HIPT(launch_shared_insert<double>(P->pick_m, P->lgB, i, P->start_y, m, st));
+        HIPT(launch_shared_insert<double>(P->pick_m, P->lgW, i, P->start_y, m, st));
         ssync(P);
     } catch (const HipError &h) {
         return fail(P, h);
