@@ -381,6 +381,7 @@ Sliced<T> upload_sliced(lp_problem *P, const HostSliced &H, const double *scaled
     Sliced<T> q{};
     q.S = H.S;
     q.split = H.split;
+    q.keep = keep_entries(nnz, P->n, P->m, sizeof(T));
     q.nb = H.nb;
     q.nblk = (int)H.blk.size();
     q.rows = H.rows;

@@ -241,6 +241,7 @@ BlockList make_blocks(lp_batch *P, const std::vector<int> &rp, const std::vector
     L.xoff[kXcds] = (int)order.size();
     L.grid = kXcds * std::min(maxper, 512);
     L.split = P->opt.split_sums == 1;   // by rows unless asked: no faster on the batched workloads
+    L.keep = keep_entries(rp.back(), P->noff[B], P->moff[B], P->mixed ? sizeof(float) : sizeof(double));
     int *d_r0 = P->arena.make<int>(L.nblk), *d_r1 = P->arena.make<int>(L.nblk);
     int *d_inst = P->arena.make<int>(L.nblk), *d_order = P->arena.make<int>(L.nblk);
     h2d(P->stream, d_r0, r0.data(), L.nblk);

@@ -706,6 +706,27 @@ __device__ __forceinline__ void average_row(const Dev<T> &d, int i, int c, T w)
     d.Kxa[i] = b + w * (kx[i] - b);
 }
 
+// A thread's up to U entries from b on of a block of cnt (slots past its end
+// re-read the last).  KEEP: with plain loads, where both matrices stay in the
+// last-level cache from one slot to the next (keep_entries); without, past the
+// caches, so that they leave them to the gathered vectors.
+template <bool KEEP, int U, typename T>
+__device__ __forceinline__ void load_entries(const int *__restrict__ ci, const T *__restrict__ v, int b, int cnt,
+                                             int (&col)[U], T (&a)[U])
+{
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int t = min((int)threadIdx.x + u * kBlock, cnt - 1);
+        if constexpr (KEEP) {
+            col[u] = ci[b + t];
+            a[u] = v[b + t];
+        } else {
+            col[u] = __builtin_nontemporal_load(ci + b + t);
+            a[u] = __builtin_nontemporal_load(v + b + t);
+        }
+    }
+}
+
 // Row extents for stream_block, of row r of a block holding rows [r0, r1)
 // and entries [b, e).  RowsPlain: a CSR's own row pointers.  RowsRel: each
 // row's start relative to its block's first entry in 16 bits (the end of the
@@ -818,11 +839,11 @@ __device__ __forceinline__ void split_row_sums(const int (&rs)[RU], const int (&
 // striding and a butterfly combining them.  A block of one row longer than
 // the block's nonzeros is summed by the whole workgroup.  Every thread of the workgroup
 // must call it.
-template <bool SPLIT = false, int U = kStreamNB / kBlock, typename T, typename ROWS>
-__device__ __forceinline__ void stream_block(const ROWS &rows, const int *__restrict__ ci,
-                                             const T *__restrict__ v, const T *__restrict__ x, int r0, int r1,
-                                             bool wave, int b, int e, T *__restrict__ out, T *prod, double *red,
-                                             SplitLds<T> *L = nullptr)
+template <bool KEEP, bool SPLIT, int U, typename T, typename ROWS>
+__device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__restrict__ ci,
+                                                const T *__restrict__ v, const T *__restrict__ x, int r0, int r1,
+                                                bool wave, int b, int e, T *__restrict__ out, T *prod, double *red,
+                                                SplitLds<T> *L)
 {
     const int cnt = e - b;
     // a multi-row block never exceeds its product's nonzeros per block (U to a
@@ -835,14 +856,7 @@ __device__ __forceinline__ void stream_block(const ROWS &rows, const int *__rest
         constexpr int RU = kStreamRB / kBlock;
         int col[U], rs[RU], re[RU];
         T a[U], g[U];
-        if (cnt > 0) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = min((int)threadIdx.x + u * kBlock, cnt - 1);
-                col[u] = __builtin_nontemporal_load(ci + b + t);
-                a[u] = __builtin_nontemporal_load(v + b + t);
-            }
-        }
+        if (cnt > 0) load_entries<KEEP>(ci, v, b, cnt, col, a);
 #pragma unroll
         for (int j = 0; j < RU; ++j) {
             const int r = min(r0 + (int)threadIdx.x + j * kBlock, r1 - 1);
@@ -910,24 +924,33 @@ __device__ __forceinline__ void stream_block(const ROWS &rows, const int *__rest
     }
 }
 
+// keep: see load_entries; small blocks are those of small matrices, always
+// kept.  A body of its own for each: one of both loads behind a branch is 1 to
+// 3% slower than either alone.
+template <bool SPLIT = false, int U = kStreamNB / kBlock, typename T, typename ROWS>
+__device__ __forceinline__ void stream_block(const ROWS &rows, const int *__restrict__ ci,
+                                             const T *__restrict__ v, const T *__restrict__ x, int r0, int r1,
+                                             bool wave, int b, int e, int keep, T *__restrict__ out, T *prod,
+                                             double *red, SplitLds<T> *L = nullptr)
+{
+    if (U < kStreamNB / kBlock || keep) stream_block_as<true, SPLIT, U>(rows, ci, v, x, r0, r1, wave, b, e, out, prod, red, L);
+    else stream_block_as<false, SPLIT, U>(rows, ci, v, x, r0, r1, wave, b, e, out, prod, red, L);
+}
+
 // Dot product of entries [b, e) of one slice (1 <= e - b <= kStreamNB): a
 // chunk of a long row.  Same load / gather / product phases as stream_block,
 // products added in registers, then across the workgroup in a fixed order;
 // every thread gets the result.  Every thread of the workgroup must call it.
 template <typename T>
 __device__ __forceinline__ T chunk_dot(const int *__restrict__ ci, const T *__restrict__ v, const T *__restrict__ x,
-                                       int b, int e, double *red)
+                                       int b, int e, int keep, double *red)
 {
     constexpr int U = kStreamNB / kBlock;
     const int cnt = e - b;
     int col[U];
     T a[U], g[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int t = min((int)threadIdx.x + u * kBlock, cnt - 1);
-        col[u] = __builtin_nontemporal_load(ci + b + t);
-        a[u] = __builtin_nontemporal_load(v + b + t);
-    }
+    if (keep) load_entries<true>(ci, v, b, cnt, col, a);
+    else load_entries<false>(ci, v, b, cnt, col, a);
 #pragma unroll
     for (int u = 0; u < U; ++u) g[u] = x[col[u]];
     T acc = T(0);
@@ -1011,13 +1034,13 @@ __device__ __forceinline__ void sliced_partial(const Sliced<T> &P, const T *__re
         const int4 q = bd[k];
         if constexpr (LONG) {
             if (q.x < 0) {   // a chunk of a long row
-                const T r = chunk_dot(P.ci, P.v, x, q.z, q.w, red);
+                const T r = chunk_dot(P.ci, P.v, x, q.z, q.w, P.keep, red);
                 if (threadIdx.x == 0) P.lpart[~q.x] = r;
                 continue;
             }
         }
         const bool wave = q.y < 0;
-        stream_block<SPLIT, U>(rows, P.ci, P.v, x, q.x, wave ? ~q.y : q.y, wave, q.z, q.w, out, prod, red, split);
+        stream_block<SPLIT, U>(rows, P.ci, P.v, x, q.x, wave ? ~q.y : q.y, wave, q.z, q.w, P.keep, out, prod, red, split);
     }
 }
 

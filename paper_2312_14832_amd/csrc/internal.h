@@ -26,6 +26,19 @@ constexpr int kSmallReg = 512;   // threads of its registers-per-thread form (tw
 constexpr size_t kSmallStageMax = 150 * 1024;   // dynamic LDS of the staged loop (of 160 KiB per CU)
 constexpr size_t kSmallRegLds = 156 * 1024;     // dynamic LDS of the registers-per-thread loop (stage + table)
 constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;  // device scratch of lp_spmv_noalloc (64 MiB per GPU)
+// Whether the products read their entries with plain loads (load_entries):
+// where what a slot touches, both matrices' entries and the vectors (9 of n, 7
+// of m), stays in the 256 MiB last-level cache from one slot to the next.
+// Larger ones only drive the vectors out of it.  Plain against nontemporal
+// loads, times of whole solves by those bytes: power-law LPs in FP64, 68 MB 4.34
+// and 4.78 ms, 204 MB 10.6 and 11.4, 238 MB 11.9 and 12.5, 272 MB 13.7 and 13.8;
+// PageRank 231 MB 11.4 and 11.7, 330 MB 16.3 and 15.3; power-law in FP32, 216 MB
+// 13.1 and 13.8; batches of LPs 202 MB 12.8 and 13.8, 302 MB 16.9 and 16.7.
+constexpr size_t kKeepBytes = (size_t)256 << 20;
+inline int keep_entries(int64_t nnz, int64_t n, int64_t m, size_t real)
+{
+    return 2 * (sizeof(int) + real) * (size_t)nnz + real * (9 * (size_t)n + 7 * (size_t)m) <= kKeepBytes;
+}
 // A row block is either a run of rows of at most kWaveRow entries (thread per
 // row; of at most kMixRow, when the row sums are split by entries, which any
 // row length suits) or up to kBlock/64 longer rows (wavefront per row); a wavefront block's
@@ -66,6 +79,7 @@ struct Sliced {
     T *lpart;         // chunk dot products of the long rows
     int nlpart;       // entries of lpart (loff[nlong])
     int split;        // 1: blocks of short rows summed split by entries, not one row per thread
+    int keep;         // 1: entries read with plain loads (keep_entries)
 };
 
 // check modes
@@ -163,6 +177,7 @@ struct BlockList {
     int xoff[kXcds + 1];
     int grid;                 // workgroups of the product kernel (a multiple of 8)
     int split;                // 1: short-row blocks summed split by entries (stream_block SPLIT)
+    int keep;                 // 1: entries read with plain loads (keep_entries)
 };
 
 // A batch of LPs concatenated block-diagonally.  Every instance's n- and
