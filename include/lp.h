@@ -133,7 +133,7 @@ typedef struct {
                                (LP_ERR_ARG). */
     int persistent;         /* small LPs: run the whole iteration loop in one workgroup (one kernel launch per
                                64 x window attempt slots, barriers in place of kernel boundaries) instead of
-                               seven launches per slot.  Eligible: both products one column slice and no row
+                               two to seven launches per slot.  Eligible: both products one column slice and no row
                                longer than 8192 entries.  -1 (default): when eligible and K, K' and the two
                                vectors the products gather fit in 150 KiB of LDS (about 5,600 nonzeros with
                                1,500 rows and columns in FP64), where it is faster than the launches; 1:
@@ -144,12 +144,13 @@ typedef struct {
                                instance has 1 to 1024 rows and columns and its K, K' and vectors fit the
                                LDS (lp_batch_loop_form); 0: the batched kernel launches. */
     int split_sums;         /* how the products' partial passes add up blocks of short rows (at most 64
-                               entries per row and column slice).  0: one row per thread, in index order;
+                               entries per row and column slice; up to 256 in split blocks where that needs
+                               clearly fewer blocks).  0: one row per thread, in index order;
                                1: split by entries, each thread adding the products of 8 consecutive
                                entries row by row and a row that crosses those chunks finished from the
                                chunks' open parts in a fixed order (a few long rows among short ones then
                                no longer hold up their wavefront); -1 (default): split in a product of at
-                               least 1024 row blocks (about 2 million nonzeros; in smaller ones the
+                               least 1024 row blocks of 2048 (about 2 million nonzeros; in smaller ones the
                                split's extra barriers cost more than they save), and with autotune the
                                other form is timed on each product's chosen layout and kept when at
                                least 3% faster (lp_layout_split).  Both forms are deterministic;
@@ -353,9 +354,10 @@ const char *lp_last_error(const lp_problem *P);
  * c, q, l, u (a parametric family, e.g. the training set of the warm-start
  * network).  The method per instance is exactly the one lp_solve runs; the
  * scaling depends on K alone, so every instance gets the same factors.  The
- * iterates of all instances are interleaved on the device, so each sparse
- * product of an iteration (K x and K'y, Sec. 2 "Restarted PDHG") reads K
- * once for all instances (an SpMM) instead of once per instance.  Host
+ * iterates are interleaved on the device in groups of up to 16 instances (32
+ * in mixed precision), so each sparse product of an iteration (K x and K'y,
+ * Sec. 2 "Restarted PDHG") reads K once for a group (an SpMM) instead of once
+ * per instance.  Host
  * pointers only; the handle allocates its own device memory (ptr_kind =
  * LP_DEVICE, a workspace or presolve is LP_ERR_ARG).
  * ------------------------------------------------------------------------ */

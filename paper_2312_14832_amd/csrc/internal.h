@@ -32,8 +32,8 @@ constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;  // device scratch of 
 // Larger ones only drive the vectors out of it.  Plain against nontemporal
 // loads, times of whole solves by those bytes: power-law LPs in FP64, 68 MB 4.34
 // and 4.78 ms, 204 MB 10.6 and 11.4, 238 MB 11.9 and 12.5, 272 MB 13.7 and 13.8;
-// PageRank 231 MB 11.4 and 11.7, 330 MB 16.3 and 15.3; power-law in FP32, 216 MB
-// 13.1 and 13.8; batches of LPs 202 MB 12.8 and 13.8, 302 MB 16.9 and 16.7.
+// PageRank 224 MB 11.4 and 11.7, 320 MB 16.3 and 15.3; power-law in FP32, 216 MB
+// 13.1 and 13.8; batches of LPs 162 MB 12.8 and 13.8, 289 MB 16.9 and 16.6.
 constexpr size_t kKeepBytes = (size_t)256 << 20;
 inline int keep_entries(int64_t nnz, int64_t n, int64_t m, size_t real)
 {
