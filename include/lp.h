@@ -251,7 +251,8 @@ int lp_spmv(lp_problem *P, int transpose, const double *in, double *out);
  * library holds on every GPU it runs on until the process ends.  It calls no
  * allocator and does not wait: the work is only enqueued on the handle's
  * stream (lp_options.stream), so the caller synchronises that stream before
- * reading out.  Nothing in the array needs to start at zero.  Every call on
+ * reading out.  in and out may overlap (a square K in place, for instance).
+ * Nothing in the array needs to start at zero.  Every call on
  * one GPU shares that GPU's array, so calls that overlap on one GPU (other
  * streams, other threads, other handles) race and must be serialised by the
  * caller.  The handle's GPU must be the current device.

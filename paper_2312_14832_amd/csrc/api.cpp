@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <functional>
 #include <memory>
 #include <string>
 #include <thread>
@@ -1305,7 +1306,9 @@ int do_spmv_noalloc(lp_problem *P, int transpose, const double *in, double *out)
     // (each slice's row blocks cover all rows; long rows use lpart, whose
     // chunks are all written), so nothing in the scratch needs clearing
     if constexpr (sizeof(T) == sizeof(double)) {
-        HIPT(launch_spmv<T>(q, (const T *)in, (T *)out, P->stream));
+        const std::less_equal<const double *> before;
+        const bool apart = before(in + lin, out) || before(out + lout, in);
+        HIPT(launch_spmv<T>(q, (const T *)in, (T *)out, P->stream, apart));
     } else {
         T *tin = (T *)(base + off[2]), *tout = (T *)(base + off[3]);
         HIPT(launch_from_double<T>(in, tin, lin, P->stream));

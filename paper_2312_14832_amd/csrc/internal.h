@@ -324,7 +324,10 @@ template <typename T> hipError_t launch_update(const Dev<T> &d, const Geo &g, hi
 template <typename T> hipError_t launch_check_reduce(const Dev<T> &d, const Geo &g, hipStream_t s);
 template <typename T> hipError_t launch_check_decide(const Dev<T> &d, const Geo &g, double Nq, double Nc, hipStream_t s);
 template <typename T> hipError_t launch_check_apply(const Dev<T> &d, const Geo &g, hipStream_t s);
-template <typename T> hipError_t launch_spmv(const Sliced<T> &P, const T *in, T *out, hipStream_t s);
+// out = P in.  apart: in and out share no memory, so a product of one slice may
+// store its rows to out while others still gather from in; otherwise the rows
+// go to the scratch vectors first, as with several slices (same bits).
+template <typename T> hipError_t launch_spmv(const Sliced<T> &P, const T *in, T *out, hipStream_t s, bool apart = true);
 template <typename T> hipError_t launch_gather_values(const double *src_vals, const int *src_pos, T *dst, int64_t len,
                                                       hipStream_t s);
 template <typename T> hipError_t launch_start(const Dev<T> &d, const double *xs, const double *ys, int cur, hipStream_t s);

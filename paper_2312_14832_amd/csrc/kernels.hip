@@ -1541,7 +1541,7 @@ static void launch_partial_plain(const Sliced<T> &P, const T *in, hipStream_t s)
 }
 
 template <typename T>
-hipError_t launch_spmv(const Sliced<T> &P, const T *in, T *out, hipStream_t s)
+hipError_t launch_spmv(const Sliced<T> &P, const T *in, T *out, hipStream_t s, bool apart)
 {
     if (P.rows <= 0) return hipSuccess;
     if (P.nlong) {
@@ -1551,11 +1551,12 @@ hipError_t launch_spmv(const Sliced<T> &P, const T *in, T *out, hipStream_t s)
         return hipGetLastError();
     }
     // one slice: its partial rows are the product (every row is in a block)
+    const bool direct = P.S == 1 && apart;
     Sliced<T> q = P;
-    if (P.S == 1) q.part = out;
+    if (direct) q.part = out;
     if (P.split) launch_partial_plain<T, true>(q, in, s);
     else launch_partial_plain<T, false>(q, in, s);
-    if (P.S > 1) hipLaunchKernelGGL((k_sum_slices<T, false>), dim3(blocks_for(P.rows)), dim3(kBlock), 0, s, P, out);
+    if (!direct) hipLaunchKernelGGL((k_sum_slices<T, false>), dim3(blocks_for(P.rows)), dim3(kBlock), 0, s, P, out);
     return hipGetLastError();
 }
 
@@ -1782,7 +1783,7 @@ hipError_t scale_csr_pair(const int *rp, const int *ci, double *kv, int m, const
     template hipError_t launch_check_reduce<T>(const Dev<T> &, const Geo &, hipStream_t);                          \
     template hipError_t launch_check_decide<T>(const Dev<T> &, const Geo &, double, double, hipStream_t);          \
     template hipError_t launch_check_apply<T>(const Dev<T> &, const Geo &, hipStream_t);                           \
-    template hipError_t launch_spmv<T>(const Sliced<T> &, const T *, T *, hipStream_t);                            \
+    template hipError_t launch_spmv<T>(const Sliced<T> &, const T *, T *, hipStream_t, bool);                      \
     template hipError_t launch_gather_probe<T>(const int *, const T *, int64_t, int, int64_t, T *, int, hipStream_t); \
     template hipError_t launch_small_loop<T>(const Dev<T> &, int, int, int, double, double, hipStream_t);        \
     template hipError_t launch_small_loop_batch<T>(const Dev<T> *, const double *, const double *, int, int,      \
