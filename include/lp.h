@@ -104,8 +104,9 @@ typedef struct {
     int autotune;           /* 1: at lp_load, time the slice count from slice_kib, then halve it (else
                                double it, to at most 32) while that keeps helping, then smaller row blocks,
                                on the actual matrix, and keep the fastest, per product (0); a candidate
-                               replaces the current choice only when at least 3% faster.  Ignored when a
-                               workspace is given.  At lp_batch_load: the row-block shape
+                               replaces the current choice only when at least 3% faster.  Where both
+                               products can be one slice, whole steps of the solve are timed to decide
+                               between that and what the products chose.  Ignored when a workspace is given.  At lp_batch_load: the row-block shape
                                (lp_batch_layout_blocks) */
     int verbose;            /* 1: messages on stderr, and one trace line per window of the solve (k, attempts,
                                restarts, eta, omega, and rel_p, rel_d, rel_gap, KKT_omega of the last check) */

@@ -45,6 +45,7 @@ int slices_for(int64_t bytes, int64_t slice_bytes)
 struct HostSliced {
     int S = 1, rows = 0, cols = 0, nb = kStreamNB, rb = kStreamRB;
     int split = 0;   // the row sums are split by entries (Sliced::split)
+    bool mixed = false;   // rows of more than kWaveRow entries stay among the short ones
     std::vector<int> rp, ci, src, brow, boff;
     std::vector<unsigned short> ro;   // per slice and row: start relative to its row block's first entry
     std::vector<int4> blk;   // per row block: first row, end row, first entry, end entry
@@ -214,7 +215,8 @@ void build_sliced(HostSliced &H, int rows, int cols, const std::vector<int> &rp,
     H.split = split == -1 ? apart >= kSplitMinBlocks * (size_t)(kStreamNB / nb) : split;
     // (a few long rows cost nothing: under a quarter more blocks, they keep
     // their wavefronts)
-    if (H.split && 4 * apart <= 5 * cut(kMixRow)) cut(kWaveRow);
+    H.mixed = H.split && 4 * apart > 5 * cut(kMixRow);
+    if (H.split && !H.mixed) cut(kWaveRow);
     // row starts relative to their block (a block holds at most kStreamNB
     // entries unless it is a single row, so the offsets fit 16 bits)
     H.ro.assign((size_t)S * (size_t)rows, 0);
@@ -383,6 +385,7 @@ Sliced<T> upload_sliced(lp_problem *P, const HostSliced &H, const double *scaled
     q.S = H.S;
     q.split = H.split;
     q.keep = keep_entries(nnz, P->n, P->m, sizeof(T));
+    q.u = kStreamNB / kBlock;
     q.nb = H.nb;
     q.nblk = (int)H.blk.size();
     q.rows = H.rows;
@@ -426,17 +429,20 @@ void free_sliced(lp_problem *P, Sliced<T> &q)
     q = Sliced<T>{};
 }
 
-// Mean time of one product (partial pass + slice sums) on a vector of ones.
+// Mean time of one product on a vector of ones, in the form a solve runs it
+// in: in the fused slot one pass, elsewhere the partial pass and slice sums,
+// one slice or several (the solve's sums are part of its next kernel).
 template <typename T>
-float time_product(lp_problem *P, const Sliced<T> &q, T *in, T *out, int64_t in_len)
+float time_product(lp_problem *P, Sliced<T> q, T *in, T *out, int64_t in_len, bool fused)
 {
     std::vector<T> ones((size_t)std::max<int64_t>(in_len, 1), T(1));
     upload(P, in, ones.data(), in_len);
+    q.u = entries_per_thread(q, fused);
     EventPair ev;
-    for (int r = 0; r < 2; ++r) HIPT(launch_spmv<T>(q, in, out, P->stream));
+    for (int r = 0; r < 2; ++r) HIPT(launch_spmv<T>(q, in, out, P->stream, fused));
     HIPT(hipEventRecord(ev.a, P->stream));
     const int reps = 5;
-    for (int r = 0; r < reps; ++r) HIPT(launch_spmv<T>(q, in, out, P->stream));
+    for (int r = 0; r < reps; ++r) HIPT(launch_spmv<T>(q, in, out, P->stream, fused));
     HIPT(hipEventRecord(ev.b, P->stream));
     HIPT(hipEventSynchronize(ev.b));
     return ev.ms() / reps;
@@ -447,63 +453,226 @@ float time_product(lp_problem *P, const Sliced<T> &q, T *in, T *out, int64_t in_
 // two processes rarely pick different layouts.
 constexpr float kTuneMargin = 0.97f;
 
-// Autotuner for one product: times the default layout, then walks the slice
-// count down by halving while that keeps helping (else up by doubling, to at
-// most 32), then tries halved nonzeros per row block and 256 rows per block at
-// the best slice count, on the actual matrix, and keeps the fastest.  The walk
-// matters on very sparse matrices with many rows: each slice adds a row
-// pointer and a partial per row, which can outweigh the L2 locality it buys.
-// Last, when split_sums is -1, it times the other form of the row sums on the
-// chosen layout (same device arrays) and keeps the faster.
+// Autotuner for one product, on the actual matrix.  slices() walks the slice
+// count from the default down by halving while that keeps helping (else up by
+// doubling, to at most 32); blocks() then tries halved nonzeros per row block,
+// 256 rows per block and, when split_sums is -1, the other form of the row
+// sums, and keeps the fastest.  The walk matters on very sparse matrices with
+// many rows: each slice adds a row pointer and a partial per row, which can
+// outweigh the L2 locality it buys.
 template <typename T>
-Sliced<T> tuned_sliced(lp_problem *P, const HostSliced &H0, const std::vector<int> &rp, const std::vector<int> &ci,
-                       const double *vals, T *in, T *out, int64_t in_len, std::vector<TuneTrial> &log, int *shape)
-{
-    Sliced<T> best = upload_sliced<T>(P, H0, vals);
-    float best_ms = time_product<T>(P, best, in, out, in_len);
-    log.push_back({H0.S, H0.nb, H0.rb, best_ms});
-    shape[0] = H0.S; shape[1] = H0.nb; shape[2] = H0.rb;
-    // time one layout; keep it if it is the fastest so far
-    auto trial = [&](int S, int nb, int rb) {
+struct Tuner {
+    lp_problem *P;
+    const char *name;
+    const std::vector<int> &rp, &ci;
+    const double *vals;
+    T *in, *out;
+    int64_t in_len;
+    int rows, cols, nb0, rb0, split0;
+    std::vector<TuneTrial> &log;
+    Sliced<T> base{}, best{};   // the default layout, and the fastest so far (base's arrays or its own)
+    int shape0[3], shape[3];
+    bool mixed0, mixed;   // HostSliced::mixed of base and best
+    float best_ms = 0;
+
+    Tuner(lp_problem *P_, const char *name_, const HostSliced &H, const std::vector<int> &rp_, const std::vector<int> &ci_,
+          const double *vals_, T *in_, T *out_, int64_t in_len_, std::vector<TuneTrial> &log_)
+        : P(P_), name(name_), rp(rp_), ci(ci_), vals(vals_), in(in_), out(out_), in_len(in_len_), rows(H.rows), cols(H.cols),
+          nb0(H.nb), rb0(H.rb), split0(H.split), log(log_), base(upload_sliced<T>(P_, H, vals_)), best(base),
+          shape0{H.S, H.nb, H.rb}, shape{H.S, H.nb, H.rb}, mixed0(H.mixed), mixed(H.mixed)
+    {
+    }
+    // put one layout in best's place
+    void take(const Sliced<T> &q, const HostSliced &H, float ms)
+    {
+        drop();
+        best = q;
+        best_ms = ms;
+        mixed = H.mixed;
+        shape[0] = H.S; shape[1] = H.nb; shape[2] = H.rb;
+    }
+    // give best's arrays back, unless they are base's
+    void drop()
+    {
+        if (best.rp != base.rp) free_sliced<T>(P, best);
+    }
+    // time one layout; keep it if it is the fastest so far by the margin
+    bool trial(int S, int nb, int rb, int split, bool fused, float margin = kTuneMargin)
+    {
         HostSliced H;
-        build_sliced(H, H0.rows, H0.cols, rp, ci, S, H0.split, nb, rb);
+        build_sliced(H, rows, cols, rp, ci, S, split, nb, rb);
         Sliced<T> q = upload_sliced<T>(P, H, vals);
-        const float ms = time_product<T>(P, q, in, out, in_len);
+        const float ms = time_product<T>(P, q, in, out, in_len, fused);
         log.push_back({S, nb, rb, ms});
-        if (ms < kTuneMargin * best_ms) {
-            free_sliced<T>(P, best);
-            best = q;
-            best_ms = ms;
-            shape[0] = S; shape[1] = nb; shape[2] = rb;
+        if (ms < margin * best_ms) {
+            take(q, H, ms);
             return true;
         }
         free_sliced<T>(P, q);
         return false;
-    };
-    bool down = false;
-    for (int S = H0.S / 2; S >= 1 && trial(S, H0.nb, H0.rb); S /= 2) down = true;
-    if (!down)
-        for (int S = H0.S * 2; S <= 32 && trial(S, H0.nb, H0.rb); S *= 2) {}
-    const int S = shape[0];
-    if (H0.nb / 2 >= 1) trial(S, H0.nb / 2, H0.rb);
-    if (H0.rb != 256) trial(S, shape[1], 256);
-    if (P->opt.split_sums == -1) {
-        Sliced<T> q = best;
-        q.split = !best.split;
-        const float ms = time_product<T>(P, q, in, out, in_len);
+    }
+    void slices(float margin)
+    {
+        best_ms = time_product<T>(P, best, in, out, in_len, false);
+        log.push_back({shape0[0], nb0, rb0, best_ms});
+        bool down = false;
+        for (int S = shape0[0] / 2; S >= 1 && trial(S, nb0, rb0, split0, false, margin); S /= 2) down = true;
+        if (!down)
+            for (int S = shape0[0] * 2; S <= 32 && trial(S, nb0, rb0, split0, false, margin); S *= 2) {}
+    }
+    // the layout this product would have in the fused slot: base's where that is one
+    void single(Sliced<T> &q, HostSliced &H)
+    {
+        if (shape0[0] == 1 && rb0 <= kFusedRB) {
+            q = base;
+            H.S = 1;
+            H.nb = nb0;
+            H.rb = rb0;
+            H.mixed = mixed0;
+            return;
+        }
+        build_sliced(H, rows, cols, rp, ci, 1, split0, nb0, std::min(rb0, kFusedRB));
+        q = upload_sliced<T>(P, H, vals);
+    }
+    void blocks(bool fused)
+    {
+        if (fused) best_ms = time_product<T>(P, best, in, out, in_len, true);
+        const int S = shape[0];
+        if (nb0 / 2 >= 1) trial(S, nb0 / 2, shape[2], split0, fused);
+        if (shape[2] > 256) trial(S, shape[1], 256, split0, fused);
+        if (P->opt.split_sums == -1) {
+            // where the two forms want other row blocks, on those of the other form
+            const int other = !best.split;
+            HostSliced H;
+            if (other) build_sliced(H, rows, cols, rp, ci, S, other, shape[1], shape[2]);
+            if (H.mixed || mixed) {
+                trial(S, shape[1], shape[2], other, fused);
+            } else {
+                Sliced<T> q = best;
+                q.split = other;
+                const float ms = time_product<T>(P, q, in, out, in_len, fused);
+                if (P->opt.verbose)
+                    std::fprintf(stderr, "[lp] layout %s row sums %s: %.3f ms against %.3f\n", name,
+                                 other ? "split by entries" : "by rows", ms, best_ms);
+                if (ms < kTuneMargin * best_ms) {
+                    best.split = other;
+                    best_ms = ms;
+                }
+            }
+        }
+        if (best.rp != base.rp) free_sliced<T>(P, base);
         if (P->opt.verbose)
-            std::fprintf(stderr, "[lp] layout %s row sums %s: %.3f ms against %.3f\n", &log == &P->tune_log_K ? "K" : "K'",
-                         q.split ? "split by entries" : "by rows", ms, best_ms);
-        if (ms < kTuneMargin * best_ms) {
-            best.split = q.split;
-            best_ms = ms;
+            for (const auto &t : log)
+                std::fprintf(stderr, "[lp] layout %s S=%d nnz/block=%d rows/block=%d: %.3f ms\n", name, t.S, t.nb, t.rb,
+                             t.ms);
+    }
+};
+
+// Whether the two products of a handle run in the fused slot, with the grids
+// that go with it: one column slice each, no long rows, two rows to a thread
+// at most.
+template <typename T>
+void set_geo(lp_problem *P)
+{
+    Dev<T> &d = P->dev<T>();
+    Geo &g = P->geo;
+    g.vb_n = (int)((P->n + kBlock - 1) / kBlock);
+    g.vb_m = (int)((P->m + kBlock - 1) / kBlock);
+    // one grid size for the elementwise solver kernels (its workgroups are the
+    // partial-sum slots); in the fused slot its second kernel's workgroups are
+    // the slots of every partial sum but the dual step's
+    g.grid = std::max(1, std::min(kMaxGrid, g.vb_n + g.vb_m));
+    auto fits = [](const Sliced<T> &A, const int *shape) { return A.S == 1 && A.nlong == 0 && shape[2] <= kFusedRB; };
+    g.fused = fits(d.K, P->shape_K) && fits(d.KT, P->shape_KT);
+    g.grid_K = std::max(1, std::min(kMaxGrid, d.K.nblk));
+    if (g.fused) g.grid = std::max(1, std::min(kMaxGrid, std::max(d.KT.nblk, g.vb_m)));
+    d.K.u = entries_per_thread(d.K, g.fused);
+    d.KT.u = entries_per_thread(d.KT, g.fused);
+}
+
+template <typename T>
+void launch_slot(lp_problem *P, int slot, int W, bool timed);
+
+// Mean time of a slot with the products K and KT in the handle, from a zero
+// start with a fixed step (so every slot is an accepted step without a check).
+// Leaves the vectors and the controller to the solve's start.
+template <typename T>
+float time_slots(lp_problem *P, const Sliced<T> &K, const int *shape_K, const Sliced<T> &KT, const int *shape_KT)
+{
+    Dev<T> &d = P->dev<T>();
+    d.K = K;
+    d.KT = KT;
+    std::copy_n(shape_K, 3, P->shape_K);
+    std::copy_n(shape_KT, 3, P->shape_KT);
+    set_geo<T>(P);
+    auto clear = [&](T *v, int64_t len) { HIPT(hipMemsetAsync(v, 0, sizeof(T) * (size_t)len, P->stream)); };
+    for (T *v : {d.xb[0], d.xb[1], d.KTyb[0], d.KTyb[1], d.xa, d.KTya}) clear(v, P->n);
+    for (T *v : {d.yb[0], d.yb[1], d.Kxb[0], d.Kxb[1], d.ya, d.Kxa}) clear(v, P->m);
+    Ctl c{};
+    c.eta = c.fixed_eta = 1e-3;
+    c.omega = 1.0;
+    c.fixed_step = 1;
+    c.check_every = 1 << 30;
+    c.max_iters = 1LL << 60;
+    upload(P, d.ctl, &c, 1);
+    constexpr int warm = 2, reps = 8;
+    EventPair ev;
+    for (int s = 0; s < warm + reps; ++s) {
+        if (s == warm) HIPT(hipEventRecord(ev.a, P->stream));
+        launch_slot<T>(P, s, warm + reps, false);
+    }
+    HIPT(hipEventRecord(ev.b, P->stream));
+    HIPT(hipEventSynchronize(ev.b));
+    return ev.ms() / reps;
+}
+
+template <typename T>
+bool small_loop_eligible(lp_problem *P);
+
+// The layouts of both products by measurement.  Where both can be a single
+// slice, whole slots decide between those two, fused, and what the products
+// chose, and any gain of a product gets it a trial: 420,000 columns and 1.05e7
+// nonzeros in FP64 have products of 67 us in one slice or two, and slots of 171
+// us fused and 153 with K in two; below 200,000 columns the two launches of the
+// fused slot win.  An LP small enough for the one-workgroup loop keeps to it.
+template <typename T>
+void tune(lp_problem *P, Tuner<T> &K, Tuner<T> &KT)
+{
+    Dev<T> &d = P->dev<T>();
+    d.K = K.base;
+    d.KT = KT.base;
+    const bool by_default = K.shape0[0] == 1 && KT.shape0[0] == 1 && K.base.nlong == 0 && KT.base.nlong == 0;
+    bool fused = by_default && small_loop_eligible<T>(P);
+    if (!fused) {
+        K.slices(by_default ? 1.0f : kTuneMargin);
+        KT.slices(by_default ? 1.0f : kTuneMargin);
+        const bool chosen = K.shape[0] == 1 && KT.shape[0] == 1 && K.base.nlong == 0 && KT.base.nlong == 0;
+        fused = by_default && chosen;
+        if (by_default != chosen) {
+            Sliced<T> k, kt;
+            HostSliced Hk, Ht;
+            K.single(k, Hk);
+            KT.single(kt, Ht);
+            const int sk[3] = {Hk.S, Hk.nb, Hk.rb}, skt[3] = {Ht.S, Ht.nb, Ht.rb};
+            const float apart = time_slots<T>(P, K.best, K.shape, KT.best, KT.shape);
+            const float one = time_slots<T>(P, k, sk, kt, skt);
+            if (P->opt.verbose) std::fprintf(stderr, "[lp] slot of one slice each: %.3f ms against %.3f\n", one, apart);
+            fused = by_default ? !(apart < kTuneMargin * one) : one < kTuneMargin * apart;
+            if (fused) {
+                K.take(k, Hk, 0);
+                KT.take(kt, Ht, 0);
+            } else {
+                if (k.rp != K.base.rp) free_sliced<T>(P, k);
+                if (kt.rp != KT.base.rp) free_sliced<T>(P, kt);
+            }
         }
     }
-    if (P->opt.verbose)
-        for (const auto &t : log)
-            std::fprintf(stderr, "[lp] layout %s S=%d nnz/block=%d rows/block=%d: %.3f ms\n",
-                         &log == &P->tune_log_K ? "K" : "K'", t.S, t.nb, t.rb, t.ms);
-    return best;
+    K.blocks(fused);
+    KT.blocks(fused);
+    d.K = K.best;
+    d.KT = KT.best;
+    std::copy_n(K.shape, 3, P->shape_K);
+    std::copy_n(KT.shape, 3, P->shape_KT);
 }
 
 template <typename T>
@@ -521,19 +690,6 @@ void setup_typed(lp_problem *P, const HostSliced &HK, const HostSliced &HT, cons
     auto tvec = [&](int64_t len) { return (T *)P->dalloc(sizeof(T) * (size_t)std::max<int64_t>(len, 1)); };
     P->tmp_n = tvec(n);
     P->tmp_m = tvec(m);
-    if (P->opt.autotune && !P->ws) {
-        d.K = tuned_sliced<T>(P, HK, rp, ci, kv64, (T *)P->tmp_n, (T *)P->tmp_m, n, P->tune_log_K, P->shape_K);
-        d.KT = tuned_sliced<T>(P, HT, tp, ti, tv64, (T *)P->tmp_m, (T *)P->tmp_n, m, P->tune_log_KT, P->shape_KT);
-    } else {
-        d.K = upload_sliced<T>(P, HK, kv64);
-        d.KT = upload_sliced<T>(P, HT, tv64);
-        P->shape_K[0] = HK.S; P->shape_K[1] = HK.nb; P->shape_K[2] = HK.rb;
-        P->shape_KT[0] = HT.S; P->shape_KT[1] = HT.nb; P->shape_KT[2] = HT.rb;
-    }
-    P->slices_K = d.K.S;
-    P->slices_KT = d.KT.S;
-    P->split_K = d.K.split;
-    P->split_KT = d.KT.split;
     if (std::is_same<T, double>::value) {
         d.cs = (const T *)cs64; d.ls = (const T *)ls64; d.us = (const T *)us64; d.qs = (const T *)qs64;
     } else {
@@ -555,6 +711,21 @@ void setup_typed(lp_problem *P, const HostSliced &HK, const HostSliced &HT, cons
     d.part_check = (double *)P->dalloc(sizeof(double) * kMaxGrid * kCheckSums);
     d.part_ray = (double *)P->dalloc(sizeof(double) * kMaxGrid * kRaySums);
     d.ctl = (Ctl *)P->dalloc(2 * sizeof(Ctl));   // two copies: the fused slot's controller goes from one to the other
+    if (P->opt.autotune && !P->ws) {
+        Tuner<T> K(P, "K", HK, rp, ci, kv64, (T *)P->tmp_n, (T *)P->tmp_m, n, P->tune_log_K);
+        Tuner<T> KT(P, "K'", HT, tp, ti, tv64, (T *)P->tmp_m, (T *)P->tmp_n, m, P->tune_log_KT);
+        tune(P, K, KT);
+    } else {
+        d.K = upload_sliced<T>(P, HK, kv64);
+        d.KT = upload_sliced<T>(P, HT, tv64);
+        P->shape_K[0] = HK.S; P->shape_K[1] = HK.nb; P->shape_K[2] = HK.rb;
+        P->shape_KT[0] = HT.S; P->shape_KT[1] = HT.nb; P->shape_KT[2] = HT.rb;
+    }
+    P->slices_K = d.K.S;
+    P->slices_KT = d.KT.S;
+    P->split_K = d.K.split;
+    P->split_KT = d.KT.split;
+    set_geo<T>(P);
 }
 
 // Host copies of lp_load's arrays when the caller passed device pointers.
@@ -758,20 +929,6 @@ int do_load(lp_problem *P, const lp_csr *K, const double *c, const double *q, co
     for (void *pp : {(void *)r, (void *)s, (void *)d_c, (void *)d_l, (void *)d_u, (void *)d_q, (void *)d_klong,
                      (void *)d_tlong})
         P->dfree(pp);
-
-    // one grid size for the elementwise solver kernels (its workgroups are the partial-sum slots)
-    Geo &g = P->geo;
-    g.vb_n = (int)((n + kBlock - 1) / kBlock);
-    g.vb_m = (int)((m + kBlock - 1) / kBlock);
-    g.grid = std::max(1, std::min(kMaxGrid, g.vb_n + g.vb_m));
-    // the fused slot: its second kernel's workgroups are the slots of every
-    // partial sum but the dual step's
-    auto fits = [](const auto &A, const int *shape) { return A.S == 1 && A.nlong == 0 && shape[2] <= kFusedRB; };
-    auto blocks = [&](bool t) { return P->mixed ? (t ? P->d32.KT.nblk : P->d32.K.nblk) : (t ? P->d64.KT.nblk : P->d64.K.nblk); };
-    g.fused = P->mixed ? fits(P->d32.K, P->shape_K) && fits(P->d32.KT, P->shape_KT)
-                       : fits(P->d64.K, P->shape_K) && fits(P->d64.KT, P->shape_KT);
-    g.grid_K = std::max(1, std::min(kMaxGrid, blocks(false)));
-    if (g.fused) g.grid = std::max(1, std::min(kMaxGrid, std::max(blocks(true), g.vb_m)));
     return LP_OK;
 }
 

@@ -937,9 +937,9 @@ __device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__r
     }
 }
 
-// keep: see load_entries; small blocks are those of small matrices, always
-// kept.  A body of its own for each: one of both loads behind a branch is 1 to
-// 3% slower than either alone.
+// keep: see load_entries; with fewer than 8 entries a thread it is always set
+// (entries_per_thread).  A body of its own for each: one of both loads behind a
+// branch is 1 to 3% slower than either alone.
 template <bool SPLIT = false, int U = kStreamNB / kBlock, typename T, typename ROWS>
 __device__ __forceinline__ void stream_block(const ROWS &rows, const int *__restrict__ ci,
                                              const T *__restrict__ v, const T *__restrict__ x, int r0, int r1,

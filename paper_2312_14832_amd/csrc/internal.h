@@ -61,6 +61,7 @@ template <typename T>
 struct Sliced {
     int S;            // column slices (a power of two)
     int nb;           // most nonzeros of one row block (unless a single row)
+    int u;            // entries per thread that its kernels hold of a row block: 8, or entries_per_thread
     int nblk;         // row blocks in total
     int rows;         // rows of the product
     int grid;         // workgroups of the partial pass (a multiple of 8 and of S)
@@ -81,6 +82,16 @@ struct Sliced {
     int split;        // 1: blocks of short rows summed split by entries, not one row per thread
     int keep;         // 1: entries read with plain loads (keep_entries)
 };
+
+// Sliced::u.  Bodies of 2 and 4 entries a thread are built for the fused slot
+// alone, and with plain loads alone (load_entries); everywhere else a row block
+// of any size runs with 8.
+template <typename T>
+int entries_per_thread(const Sliced<T> &q, bool fused)
+{
+    if (!fused || !q.keep) return kStreamNB / kBlock;
+    return q.nb <= 2 * kBlock ? 2 : q.nb <= 4 * kBlock ? 4 : kStreamNB / kBlock;
+}
 
 // check modes
 enum : int { MODE_NONE = 0, MODE_CHECK = 1, MODE_INIT = 2, MODE_FINAL = 3, MODE_RESUME = 4 };

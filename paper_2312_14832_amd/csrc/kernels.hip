@@ -1526,14 +1526,11 @@ hipError_t launch_gather_probe(const int *idx, const T *x, int64_t per_slice, in
     return hipGetLastError();
 }
 
-// the entries per thread of a row block of at most nb nonzeros
-static inline int block_u(int nb) { return nb <= 2 * kBlock ? 2 : nb <= 4 * kBlock ? 4 : 8; }
-
 template <typename T, bool SPLIT>
 static void launch_partial_plain(const Sliced<T> &P, const T *in, hipStream_t s)
 {
     const dim3 g(P.grid), t(kBlock);
-    switch (block_u(P.nb)) {
+    switch (P.u) {
     case 2: hipLaunchKernelGGL((k_partial_plain<T, false, SPLIT, 2>), g, t, 0, s, P, in); break;
     case 4: hipLaunchKernelGGL((k_partial_plain<T, false, SPLIT, 4>), g, t, 0, s, P, in); break;
     default: hipLaunchKernelGGL((k_partial_plain<T, false, SPLIT>), g, t, 0, s, P, in); break;
@@ -1564,7 +1561,7 @@ template <typename T, bool SPLIT>
 static void launch_fused_dual_t(const Dev<T> &d, const Geo &g, Ctl *ctl, hipStream_t s)
 {
     const dim3 grid(g.grid_K + 1), t(kBlock);
-    switch (block_u(d.K.nb)) {
+    switch (d.K.u) {
     case 2: hipLaunchKernelGGL((k_fused_dual<T, 2, SPLIT>), grid, t, 0, s, d, ctl); break;
     case 4: hipLaunchKernelGGL((k_fused_dual<T, 4, SPLIT>), grid, t, 0, s, d, ctl); break;
     default: hipLaunchKernelGGL((k_fused_dual<T, 8, SPLIT>), grid, t, 0, s, d, ctl); break;
@@ -1583,7 +1580,7 @@ template <typename T, bool SPLIT>
 static void launch_fused_update_t(const Dev<T> &d, const Geo &g, const Ctl *in, const double *pin, Ctl *out, hipStream_t s)
 {
     const dim3 grid(g.grid), t(kBlock);
-    switch (block_u(d.KT.nb)) {
+    switch (d.KT.u) {
     case 2: hipLaunchKernelGGL((k_fused_update<T, 2, SPLIT>), grid, t, 0, s, d, in, pin, out, g.grid_K, g.vb_m); break;
     case 4: hipLaunchKernelGGL((k_fused_update<T, 4, SPLIT>), grid, t, 0, s, d, in, pin, out, g.grid_K, g.vb_m); break;
     default: hipLaunchKernelGGL((k_fused_update<T, 8, SPLIT>), grid, t, 0, s, d, in, pin, out, g.grid_K, g.vb_m); break;
