@@ -169,6 +169,11 @@ __device__ __forceinline__ int group_slots(const SDev<T> &S, int g, int grid)
 // vectors of `rows` rows that start at `base`; used: tiles of the earlier groups.
 struct Walk {
     int base, lo, hi, step;
+    // one group (of few instances), every workgroup on all of it
+    __device__ __forceinline__ explicit Walk(int len)
+        : base(0), lo((int)(blockIdx.x * kBlock + threadIdx.x)), hi(len), step((int)(gridDim.x * kBlock))
+    {
+    }
     __device__ __forceinline__ Walk(const Share &w, int g, int rows, int &used)
     {
         const int len = rows << w.lgW;
@@ -186,7 +191,19 @@ struct Walk {
         hi = base + min(t1 * kBlock, len);
         step = w.P * kBlock;
     }
+    // whether the workgroup has any element
+    __device__ __forceinline__ bool any() const { return lo - (int)threadIdx.x < hi; }
 };
+
+// the partials of a workgroup without elements of a group, as store_inst_partials stores them
+template <int NV>
+__device__ __forceinline__ void store_zero_partials(int W, int b0, int slot, int slots, double *out)
+{
+    const int t = (int)threadIdx.x;
+    if (t >= W) return;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) out[((size_t)(b0 + t) * slots + slot) * NV + k] = 0.0;
+}
 
 // The buffer that a group's lanes gather from: each lane's own c where it
 // takes part, and the first such lane's where it does not (finished and padded
@@ -200,24 +217,37 @@ __device__ __forceinline__ int gather_buffer(unsigned long long part, bool mine,
 // K~ x' for every instance fused with the dual step.
 // The step's own operands are loaded before the row's product so their
 // latency overlaps the gathers.  Workgroup 0 lowers the check gate (this
-// slot's step decisions raise it).
+// slot's step decisions raise it).  W = 0 (here and in sk_update): at most four
+// instances, in one group, which takes the plain walk and whose lanes of
+// finished instances have nothing to load for others.  By eighths and with the
+// groups' set-up, one instance of 3e5 columns took 44 us here, with these 35.
 template <typename T, int W>
 __global__ __launch_bounds__(kBlock) void sk_dual(SDev<T> S)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) *S.gate = 0;
     const Dev<T> &d = S.d;
     const Share w(S);
-    const int b = w.column();
+    const int b = w.column(), g0 = W ? w.g0 : 0, g1 = W ? w.g1 : 0;
     int used = 0;
-    for (int g = w.g0; g <= w.g1; ++g) {
-        const Walk r(w, g, S.m, used);
+    for (int g = g0; g <= g1; ++g) {
+        Walk r = W ? Walk(w, g, S.m, used) : Walk(S.m << S.lgW);
+        if (W && !r.any()) {   // the same for the whole workgroup
+            store_zero_partials<2>(w.W, g * w.W, w.slot(g), (int)gridDim.x, d.part_dual);
+            continue;
+        }
         const Ctl *ctl = S.ctl + g * w.W + b;
         double v[2] = {0.0, 0.0};
         const bool run = !ctl->done;
-        const unsigned long long part = __ballot(run);   // the wavefront holds every instance of the group
-        if (!part) continue;   // all finished: their partials are not read
         const int c = ctl->cur;
-        const T *x = pick(d.xb, gather_buffer(part, run, c) ^ 1) + ((size_t)g * S.n << S.lgW);
+        int cx = c;
+        if constexpr (W > 0) {
+            const unsigned long long part = __ballot(run);   // the wavefront holds every instance of the group
+            if (!part) continue;   // all finished: their partials are not read
+            cx = gather_buffer(part, run, c);
+        } else if (!run) {
+            r.hi = 0;
+        }
+        const T *x = pick(d.xb, cx ^ 1) + ((size_t)g * S.n << S.lgW);
         const T *y = pick(d.yb, c), *kx = pick(d.Kxb, c);
         T *yn = pick(d.yb, c ^ 1), *kxn = pick(d.Kxb, c ^ 1);
         const T sigma = (T)(ctl->eta * ctl->omega);
@@ -228,14 +258,14 @@ __global__ __launch_bounds__(kBlock) void sk_dual(SDev<T> S)
             // the dual step of DualEpi
             T val = yo + sigma * (qi - T(2) * s + ko);
             if (i >= S.m1 && val < T(0)) val = T(0);
-            if (!run) continue;
+            if (W && !run) continue;
             yn[e] = val;
             kxn[e] = s;
             const double dd = (double)val - (double)yo;
             v[0] += dd * dd;
             v[1] += dd * ((double)s - (double)ko);
         }
-        store_inst_partials<2>(v, w.W, g * w.W, w.slot(g), (int)gridDim.x, d.part_dual);
+        store_inst_partials<2>(v, w.W, g * w.W, W ? w.slot(g) : (int)blockIdx.x, (int)gridDim.x, d.part_dual);
     }
 }
 
@@ -266,20 +296,26 @@ __global__ __launch_bounds__(kBlock) void sk_update(SDev<T> S)
 {
     const Dev<T> &d = S.d;
     const Share sh(S);
-    const int b = sh.column();
+    const int b = sh.column(), g0 = W ? sh.g0 : 0, g1 = W ? sh.g1 : 0;
     int used_n = 0, used_m = 0;
-    for (int g = sh.g0; g <= sh.g1; ++g) {
-        const Walk rn(sh, g, S.n, used_n), rm(sh, g, S.m, used_m);
+    for (int g = g0; g <= g1; ++g) {
+        const Walk rn = W ? Walk(sh, g, S.n, used_n) : Walk(S.n << S.lgW);
+        const Walk rm = W ? Walk(sh, g, S.m, used_m) : Walk(S.m << S.lgW);
+        if (W && !rn.any() && !rm.any()) {
+            store_zero_partials<1>(sh.W, g * sh.W, sh.slot(g), (int)gridDim.x, d.part_primal);
+            continue;
+        }
         const Ctl *ctl = S.ctl + g * sh.W + b;
         double v[1] = {0.0};
         const bool run = !ctl->done, accepted = run && ctl->accepted;
-        if (!__ballot(run)) continue;   // the wavefront holds every instance of the group: all finished
+        if (W && !__ballot(run)) continue;   // the wavefront holds every instance of the group: all finished
         const int c = ctl->cur;
         const T tau = (T)(ctl->eta / ctl->omega);
         if (run && !accepted)
             for (int e = rn.lo; e < rn.hi; e += rn.step) primal_elem(d, c, tau, e, v[0]);
-        if (const unsigned long long part = __ballot(accepted)) {
-            const T *x = pick(d.xb, c), *y = pick(d.yb, gather_buffer(part, accepted, c)) + rm.base;
+        const unsigned long long part = W ? __ballot(accepted) : accepted;
+        if (part) {
+            const T *x = pick(d.xb, c), *y = pick(d.yb, W ? gather_buffer(part, accepted, c) : c) + rm.base;
             T *kty = pick(d.KTyb, c), *xn = pick(d.xb, c ^ 1);
             const T w = (T)ctl->avg_w;
             const bool primal = ctl->mode == MODE_NONE;
@@ -288,7 +324,7 @@ __global__ __launch_bounds__(kBlock) void sk_update(SDev<T> S)
                 const T xj = x[e], a = d.xa[e], bb = d.KTya[e];
                 const T cj = d.cs[e], lj = d.ls[e], uj = d.us[e];
                 const T s = shared_row<T, W>(S.tci, S.tv, y, S.trp[j], S.trp[j + 1], S.lgW, b);
-                if (!accepted) continue;
+                if (W && !accepted) continue;
                 // the averages and next primal trial of UpdateEpi
                 kty[e] = s;
                 d.xa[e] = a + w * (xj - a);
@@ -303,7 +339,7 @@ __global__ __launch_bounds__(kBlock) void sk_update(SDev<T> S)
             if (accepted)
                 for (int e = rm.lo; e < rm.hi; e += rm.step) average_row(d, e, c, w);
         }
-        store_inst_partials<1>(v, sh.W, g * sh.W, sh.slot(g), (int)gridDim.x, d.part_primal);
+        store_inst_partials<1>(v, sh.W, g * sh.W, W ? sh.slot(g) : (int)blockIdx.x, (int)gridDim.x, d.part_primal);
     }
 }
 
