@@ -478,26 +478,34 @@ __global__ __launch_bounds__(64 * WR * WC, WM * WN > 8 ? 1 : 2) void k_gemm_mfma
     }
 }
 
-// Output tile of a BF16 product with M x N outputs in `splits` parts: the one
-// with the least (workgroups per CU) x (tile area) / (the rate the tile
-// reaches on a full GPU, of the large one's at 8192^3).  A CU holds one
-// 256-tile, so those come in whole waves; of the smaller ones it runs several
-// at once.  Measured (us, 64 / 128 / 256): 4096^3 309 / 205 / 146, 8192^3
-// 2004 / 1310 / 1008, 2000 x 3000 x 1500 75 / 67 / 84, 1000 x 3001 x 777
-// 42 / 47 / 69, 256 x 1024 x 1024 27 / 41 / 63 (host call included, about 12).
-inline int mfma_tile(int M, int N, int splits)
+// Output tile of a BF16 product with M x N outputs in `splits` parts of kps of K
+// each: the one with the least time as fitted to measurements of each tile (34
+// shapes of 64 x 30001 to 6000 x 6000, K 64 to 4096, all four forms): a part of
+// the call, one per wave of 256 workgroups (one to a CU), one per k and one per
+// k and wave.  A smaller tile costs a call less, a larger one an output.  A CU
+// holds one 256-tile, so those come in whole waves; of the smaller ones it runs
+// several at once, and a part of a wave costs less than a whole one (fill).
+// Measured (us, 64 / 128 / 256, host call included): 4096^3 234 / 173 / 138,
+// 3000 x 3000 x 4096 158 / 136 / 117, 4200 x 4100 x 1500 161 / 118 / 126, 2000 x
+// 3000 x 1500 67 / 57 / 66, 1000 x 3001 x 777 39 / 38 / 52, 256 x 1024 x 777 25 /
+// 35 / 48.
+inline int mfma_tile(int M, int N, int kps, int splits)
 {
-    const int side[3] = {64, 128, 256};
-    const double rate[3] = {0.5, 0.75, 1.0};
-    int best = 64;
+    const struct {
+        int side;
+        double fill, call, wave, k, wave_k;   // the last four in us
+    } tiles[3] = {{64, 0.75, 21.0, 0.66, 0.0004, 0.00404},
+                  {128, 0.5, 21.2, 3.18, 0.0013, 0.01017},
+                  {256, 1.0, 18.9, 10.7, -0.0061, 0.03015}};
+    int best = 0;
     double cost = 0.0;
-    for (int i = 0; i < 3; ++i) {
-        const int64_t T = side[i], tiles = (int64_t)((M + T - 1) / T) * ((N + T - 1) / T) * splits;
-        const double fill = std::max(1.0, (double)tiles / 256.0);
-        const double c = (side[i] == 256 ? std::ceil(fill) : fill) * (double)(T * T) / rate[i];
-        if (i == 0 || c < cost) {
+    for (const auto &t : tiles) {
+        const int64_t n = (int64_t)((M + t.side - 1) / t.side) * ((N + t.side - 1) / t.side) * splits;
+        const double even = (double)n / 256.0, waves = std::max(1.0, even + t.fill * (std::ceil(even) - even));
+        const double c = t.call + t.wave * waves + (t.k + t.wave_k * waves) * kps;
+        if (best == 0 || c < cost) {
             cost = c;
-            best = side[i];
+            best = t.side;
         }
     }
     return best;
@@ -519,7 +527,7 @@ void launch_mfma_tile(const GemmArgs &g, int splits, hipStream_t st)
 template <bool AK, bool BKC>
 void launch_mfma(const GemmArgs &g, int splits, hipStream_t st)
 {
-    switch (mfma_tile(g.M, g.N, splits)) {
+    switch (mfma_tile(g.M, g.N, std::min(g.kps, g.K), splits)) {
     case 256: launch_mfma_tile<AK, BKC, 2, 4, 4, 2, 1>(g, splits, st); break;
     case 128: launch_mfma_tile<AK, BKC, 2, 2, 2, 2, 2>(g, splits, st); break;
     default:
