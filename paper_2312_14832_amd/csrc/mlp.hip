@@ -168,7 +168,8 @@ __global__ __launch_bounds__(256) void k_gemm_fp32(const float *A, int lda, cons
         }
 }
 
-// Output tile of an FP32 product: 128 from four such workgroups to a CU on.
+// Output tile of an FP32 product: 128 from four such workgroups to a CU on (a
+// product in parts stays below that, see splits_for).
 // Measured (us, 64 / 128): 4096^3, 1024 tiles of 128, 1860 / 1768; 2048^3, 256
 // of them, 271 / 398; 1000 x 3001 x 777 114 / 178.
 inline int fp32_tile(int M, int N, int splits)
@@ -766,15 +767,15 @@ __global__ void k_mse(const float *Z, const float *Zs, float *dZ, int64_t len, d
 
 // What follows a layer's input gradient [rows x cols], in one pass over it:
 // its parts added in order (one part: as it is), zeroed where H <= 0 (H null:
-// not), stored as FP32 (dY; null: not) and bfloat16 (dYb; null: not), and its
-// column sums over each `chunk` rows (the bias gradient of the layer below,
-// which k_grad_finish completes).  A workgroup takes 64 columns of one chunk,
-// four threads to a column, each adding every fourth row in order.  These were
-// four launches, the column sums alone 50 us on 256 x 1024 values (a thread
+// not), stored as T (FP32, where dY may be the one part itself, or bfloat16),
+// and its column sums over each `chunk` rows (the bias gradient of the layer
+// below, which k_grad_finish completes).  A workgroup takes 64 columns of one
+// chunk, four threads to a column, each adding every fourth row in order.  These
+// were four launches, the column sums alone 50 us on 256 x 1024 values (a thread
 // per column, four workgroups).
-__global__ __launch_bounds__(256) void k_dy(const float *__restrict__ part, int parts, const float *__restrict__ H,
-                                            float *dY, uint16_t *__restrict__ dYb, float *__restrict__ cpart, int rows,
-                                            int cols, int chunk)
+template <typename T>
+__global__ __launch_bounds__(256) void k_dy(const float *part, int parts, const float *__restrict__ H, T *dY,
+                                            float *__restrict__ cpart, int rows, int cols, int chunk)
 {
     __shared__ float sh[4][64];
     const int tc = (int)threadIdx.x & 63, tr = (int)threadIdx.x >> 6;
@@ -789,8 +790,8 @@ __global__ __launch_bounds__(256) void k_dy(const float *__restrict__ part, int 
 #pragma unroll 16
             for (int z = 1; z < parts; ++z) v += part[z * len + i];
             if (H && !(H[i] > 0.0f)) v = 0.0f;
-            if (dY) dY[i] = v;
-            if (dYb) dYb[i] = f2bf(v);
+            if constexpr (sizeof(T) == sizeof(float)) dY[i] = v;
+            else dY[i] = f2bf(v);
             sum += v;
         }
     }
@@ -992,9 +993,13 @@ void forward(lpw_net *N, const float *X, int B, int layers, float *Z)
 void launch_dy(lpw_net *N, int l, const float *part, int parts, const float *H, int B)
 {
     const int cols = N->dout[l], chunk = N->chunk[l];
-    hipLaunchKernelGGL(k_dy, dim3((cols + 63) / 64, (B + chunk - 1) / chunk), dim3(256), 0, N->st, part, parts, H,
-                       use_bf(N) ? nullptr : N->dAct[l + 1], use_bf(N) ? N->dActb[l + 1] : nullptr, N->cpart[l], B, cols,
-                       chunk);
+    const dim3 grid((cols + 63) / 64, (B + chunk - 1) / chunk);
+    if (use_bf(N))
+        hipLaunchKernelGGL(k_dy<uint16_t>, grid, dim3(256), 0, N->st, part, parts, H, N->dActb[l + 1], N->cpart[l], B, cols,
+                           chunk);
+    else
+        hipLaunchKernelGGL(k_dy<float>, grid, dim3(256), 0, N->st, part, parts, H, N->dAct[l + 1], N->cpart[l], B, cols,
+                           chunk);
     HIPT(hipGetLastError());
 }
 
