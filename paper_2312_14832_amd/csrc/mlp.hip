@@ -38,8 +38,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
 // float -> bfloat16, round to nearest even (NaN kept quiet)
 __device__ __forceinline__ uint16_t f2bf(float f)
 {
