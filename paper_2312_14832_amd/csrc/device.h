@@ -763,7 +763,7 @@ constexpr unsigned short kNoRow = 0xFFFF;
 // heads are in LDS and a barrier; rs, re hold the extents of the thread's
 // rows r0 + t + kBlock j, which it stores to out at the end.  See
 // stream_block.
-template <int U, int RU, typename T>
+template <int U, bool LOCAL, int RU, typename T>
 __device__ __forceinline__ void split_row_sums(const int (&rs)[RU], const int (&re)[RU], int r0, int r1, int b,
                                                int cnt, T *__restrict__ out, T *prod, SplitLds<T> *L)
 {
@@ -831,7 +831,7 @@ __device__ __forceinline__ void split_row_sums(const int (&rs)[RU], const int (&
 #pragma unroll
     for (int j = 0; j < RU; ++j) {
         const int r = r0 + t + j * kBlock;
-        if (r < r1) out[r] = rs[j] == re[j] ? T(0) : prod[rs[j] - b];
+        if (r < r1) out[LOCAL ? r - r0 : r] = rs[j] == re[j] ? T(0) : prod[rs[j] - b];
     }
 }
 
@@ -850,9 +850,9 @@ __device__ __forceinline__ void split_row_sums(const int (&rs)[RU], const int (&
 // barrier), then every thread stores its rows as before.  In a block of long
 // rows (wave set, at most kBlock/64) each wavefront sums one row, lanes
 // striding and a butterfly combining them.  A block of one row longer than
-// the block's nonzeros is summed by the whole workgroup.  Every thread of the workgroup
-// must call it.
-template <bool KEEP, bool SPLIT, int U, typename T, typename ROWS>
+// the block's nonzeros is summed by the whole workgroup.  out holds all rows, or
+// this block's alone (LOCAL).  Every thread of the workgroup must call it.
+template <bool KEEP, bool SPLIT, int U, bool LOCAL, typename T, typename ROWS>
 __device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__restrict__ ci,
                                                 const T *__restrict__ v, const T *__restrict__ x, int r0, int r1,
                                                 bool wave, int b, int e, T *__restrict__ out, T *prod, double *red,
@@ -900,7 +900,7 @@ __device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__r
         }
         __syncthreads();
         if (SPLIT && !wave) {
-            split_row_sums<U>(rs, re, r0, r1, b, cnt, out, prod, L);
+            split_row_sums<U, LOCAL>(rs, re, r0, r1, b, cnt, out, prod, L);
         } else if (!wave) {
 #pragma unroll
             for (int j = 0; j < RU; ++j) {
@@ -908,7 +908,7 @@ __device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__r
                 if (r < r1) {
                     T acc = T(0);
                     for (int p = rs[j] - b; p < re[j] - b; ++p) acc += prod[p];
-                    out[r] = acc;
+                    out[LOCAL ? r - r0 : r] = acc;
                 }
             }
         } else {
@@ -922,7 +922,7 @@ __device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__r
                 // the L2)
                 for (int p = rows.start(r, b) - b + lane; p < p1; p += 64) acc += prod[p];
                 acc = wave_butterfly(acc);
-                if (lane == 0) out[r] = acc;
+                if (lane == 0) out[LOCAL ? r - r0 : r] = acc;
             }
         }
         __syncthreads();
@@ -932,7 +932,7 @@ __device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__r
         acc = wave_butterfly(acc);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = (double)acc;
         __syncthreads();
-        if (threadIdx.x == 0) out[r0] = (T)(((red[0] + red[1]) + red[2]) + red[3]);
+        if (threadIdx.x == 0) out[LOCAL ? 0 : r0] = (T)(((red[0] + red[1]) + red[2]) + red[3]);
         __syncthreads();
     }
 }
@@ -940,14 +940,16 @@ __device__ __forceinline__ void stream_block_as(const ROWS &rows, const int *__r
 // keep: see load_entries; with fewer than 8 entries a thread it is always set
 // (entries_per_thread).  A body of its own for each: one of both loads behind a
 // branch is 1 to 3% slower than either alone.
-template <bool SPLIT = false, int U = kStreamNB / kBlock, typename T, typename ROWS>
+template <bool SPLIT = false, int U = kStreamNB / kBlock, bool LOCAL = false, typename T, typename ROWS>
 __device__ __forceinline__ void stream_block(const ROWS &rows, const int *__restrict__ ci,
                                              const T *__restrict__ v, const T *__restrict__ x, int r0, int r1,
                                              bool wave, int b, int e, int keep, T *__restrict__ out, T *prod,
                                              double *red, SplitLds<T> *L = nullptr)
 {
-    if (U < kStreamNB / kBlock || keep) stream_block_as<true, SPLIT, U>(rows, ci, v, x, r0, r1, wave, b, e, out, prod, red, L);
-    else stream_block_as<false, SPLIT, U>(rows, ci, v, x, r0, r1, wave, b, e, out, prod, red, L);
+    if (U < kStreamNB / kBlock || keep)
+        stream_block_as<true, SPLIT, U, LOCAL>(rows, ci, v, x, r0, r1, wave, b, e, out, prod, red, L);
+    else
+        stream_block_as<false, SPLIT, U, LOCAL>(rows, ci, v, x, r0, r1, wave, b, e, out, prod, red, L);
 }
 
 // Dot product of entries [b, e) of one slice (1 <= e - b <= kStreamNB): a

@@ -307,8 +307,8 @@ __device__ __forceinline__ void fused_rows(const Sliced<T> &P, const T *__restri
                                            SplitLds<T> *split)
 {
     const bool wave = q.y < 0;
-    stream_block<SPLIT, U>(RowsRel{P.ro}, P.ci, P.v, x, q.x, wave ? ~q.y : q.y, wave, q.z, q.w, P.keep, L.row - q.x, L.prod,
-                           L.red, split);
+    stream_block<SPLIT, U, true>(RowsRel{P.ro}, P.ci, P.v, x, q.x, wave ? ~q.y : q.y, wave, q.z, q.w, P.keep, L.row, L.prod,
+                                 L.red, split);
 }
 
 // K x' and the dual step.  The last workgroup makes the step rule's factors
