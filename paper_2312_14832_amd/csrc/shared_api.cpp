@@ -23,7 +23,11 @@ using namespace pdlp;
 
 namespace {
 constexpr int kNScalars = 16;
-constexpr int kMaxShared = kBlock;   // instances per handle (the interleave width is at most one workgroup)
+// Most instances of a handle, and the groups they can make (16 or 32 wide from
+// 16 instances on): a group's place is found by a reciprocal that is exact for
+// up to 64 of them (SDev::over_G)
+constexpr int kMaxShared = kBlock;
+static_assert(kMaxShared / 16 <= 64, "over_G is exact for these groups");
 }  // namespace
 
 struct lp_shared {
@@ -691,7 +695,7 @@ int lp_shared_load(lp_shared **out, int32_t count, const lp_csr *K, const double
     P->B = count;
     int64_t pow2 = 1;
     while (pow2 < count) pow2 <<= 1;
-    // interleaved vectors and element indices stay below 2^30
+    // interleaved vectors and element indices stay below 2^30 (Bp is at most pow2)
     if ((K->n + 1) * pow2 >= (int64_t(1) << 30) || (K->m + 1) * pow2 >= (int64_t(1) << 30))
         return LP_ERR_TOO_LARGE;
     // A group's row of a vector is a cache line: 16 instances in FP64, 32 in
