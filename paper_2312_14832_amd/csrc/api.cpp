@@ -178,14 +178,13 @@ void build_sliced(HostSliced &H, int rows, int cols, const std::vector<int> &rp,
     // so a split product keeps those rows in the runs: 60 us.
     std::vector<std::vector<int4>> bs((size_t)S);
     const int T2 = std::max(1, std::min(host_threads(), S));
-    auto cut = [&](int short_max) {
+    auto cut = [&](std::vector<std::vector<int4>> &to, int short_max) {
         run_threads(T2, [&](int t) {
             std::vector<int> brow;
             std::vector<char> wave;
             for (int sl = t; sl < S; sl += T2) {
                 const int *r = &H.rp[(size_t)sl * (rows + 1)];
-                std::vector<int4> &out = bs[(size_t)sl];
-                out.clear();
+                std::vector<int4> &out = to[(size_t)sl];
                 auto plain = [&](int r_begin, int r_end) {
                     brow.assign(1, r_begin);
                     wave.clear();
@@ -208,15 +207,22 @@ void build_sliced(HostSliced &H, int rows, int cols, const std::vector<int> &rp,
             }
         });
         size_t n = 0;
-        for (const auto &b : bs) n += b.size();
+        for (const auto &b : to) n += b.size();
         return n;
     };
-    const size_t apart = cut(kWaveRow);
+    const size_t apart = cut(bs, kWaveRow);
     H.split = split == -1 ? apart >= kSplitMinBlocks * (size_t)(kStreamNB / nb) : split;
     // (a few long rows cost nothing: under a quarter more blocks, they keep
     // their wavefronts)
-    H.mixed = H.split && 4 * apart > 5 * cut(kMixRow);
-    if (H.split && !H.mixed) cut(kWaveRow);
+    H.mixed = false;
+    bool waves = false;   // whether there are any
+    for (const auto &b : bs)
+        waves = waves || std::any_of(b.begin(), b.end(), [](const int4 &q) { return q.x >= 0 && q.y < 0; });
+    if (H.split && waves) {
+        std::vector<std::vector<int4>> together((size_t)S);
+        H.mixed = 4 * apart > 5 * cut(together, kMixRow);
+        if (H.mixed) bs.swap(together);
+    }
     // row starts relative to their block (a block holds at most kStreamNB
     // entries unless it is a single row, so the offsets fit 16 bits)
     H.ro.assign((size_t)S * (size_t)rows, 0);
