@@ -80,6 +80,7 @@ struct lp_batch {
     // fetched together when results are read in order (do_batch_result)
     std::vector<double> ahead_x, ahead_y, ahead_lam;
     int ahead_lo = 0, ahead_hi = 0;
+    int ahead_has = 0;                     // what of them: bit 0 x, 1 y, 2 lambda
     int ahead_count = 0, ahead_next = 0;   // instances of the last fetch; the one after it
 
     template <typename T> BDev<T> &dev();
@@ -725,7 +726,7 @@ int do_batch_solve(lp_batch *P, double tol, int64_t max_iters, double time_limit
     const int64_t N = P->Ntot, M = P->Mtot;
     auto t0 = std::chrono::steady_clock::now();
     auto elapsed = [&] { return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count(); };
-    P->ahead_lo = P->ahead_hi = P->ahead_count = P->ahead_next = 0;   // the points fetched ahead were the last solve's
+    P->ahead_lo = P->ahead_hi = P->ahead_has = P->ahead_count = P->ahead_next = 0;   // the points fetched ahead were the last solve's
     // a solve starts with every instance's chunks and blocks in the lists
     // (the start products below need all of them)
     const bool narrowed = P->active >= 0;
@@ -898,27 +899,42 @@ void unscale_points(lp_batch *P, int i, int count)
     HIPT(launch_result<T>(v, P->stage_n0, P->stage_m, P->stage_n1, P->stream));
 }
 
-// Most values of one fetch of several instances' points
-constexpr int64_t kAheadValues = (int64_t)4 << 17;   // 4 MiB of doubles
+// Most values of one fetch of several instances' points: 2 MiB of doubles.  A
+// fetch saves launches and waits and costs a copy on the host.  Reading every
+// point in order, all of it or x alone (us; one launch and copies a member /
+// fetches of at most 1, 2 and 4 MiB): 32 LPs of 20,000 to 40,000 columns 2527 and
+// 1500 / 2066 and 722, 1660 and 734, 1662 and 736; 16 of 60,000 to 120,000 2089 and
+// 1193 / 1920 and 888, 1925 and 1040, 2398 and 956.
+constexpr int64_t kAheadValues = (int64_t)1 << 18;
 
 // The point of instance i.  A program that reads every instance's result asks
 // for them one after another, and each used to cost a launch over the whole
 // batch, three copies and a wait (256 LPs of 300 to 1000 columns: 17 of the
 // 20 ms that their solve and results took).  Read in order, they come in
-// fetches of 1, 2, 4, ... instances up to 4 MiB; out of order, one by one.
+// fetches of 1, 2, 4, ... instances up to kAheadValues, of the vectors that the
+// call asks for (others follow for the same instances once they are asked for);
+// out of order, one by one.
 template <typename T>
 void batch_point(lp_batch *P, int i, double *x, double *y, double *lam)
 {
     hipStream_t st = P->stream;
-    if (i < P->ahead_lo || i >= P->ahead_hi) {
-        int count = i > 0 && i == P->ahead_next ? 2 * P->ahead_count : 1;
-        count = std::min(count, P->B - i);
-        auto values = [&](int k) { return 2 * (P->noff[i + k] - P->noff[i]) + P->moff[i + k] - P->moff[i]; };
-        while (count > 1 && values(count) > kAheadValues) --count;
-        P->ahead_lo = P->ahead_hi = 0;
-        P->ahead_count = count;
-        P->ahead_next = i + count;
-        unscale_points<T>(P, i, count);
+    const bool in = i >= P->ahead_lo && i < P->ahead_hi;
+    int want = (x ? 1 : 0) | (y ? 2 : 0) | (lam ? 4 : 0);
+    if (in) want &= ~P->ahead_has;
+    if (want) {
+        int first = P->ahead_lo, count = P->ahead_hi - P->ahead_lo;
+        if (!in) {
+            first = i;
+            count = std::min(i > 0 && i == P->ahead_next ? 2 * P->ahead_count : 1, P->B - i);
+            auto values = [&](int k) {
+                return ((x ? 1 : 0) + (lam ? 1 : 0)) * (P->noff[i + k] - P->noff[i]) + (y ? P->moff[i + k] - P->moff[i] : 0);
+            };
+            while (count > 1 && values(count) > kAheadValues) --count;
+            P->ahead_lo = P->ahead_hi = P->ahead_has = 0;
+            P->ahead_count = count;
+            P->ahead_next = i + count;
+        }
+        unscale_points<T>(P, first, count);
         if (count == 1) {
             if (x) d2h(st, x, (const double *)P->stage_n0, P->n[i]);
             if (lam) d2h(st, lam, (const double *)P->stage_n1, P->n[i]);
@@ -926,16 +942,18 @@ void batch_point(lp_batch *P, int i, double *x, double *y, double *lam)
             bsync(P);
             return;
         }
-        const int64_t n = P->noff[i + count] - P->noff[i], m = P->moff[i + count] - P->moff[i];
-        P->ahead_x.resize((size_t)n);
-        P->ahead_lam.resize((size_t)n);
-        P->ahead_y.resize((size_t)m);
-        d2h(st, P->ahead_x.data(), (const double *)P->stage_n0, n);
-        d2h(st, P->ahead_lam.data(), (const double *)P->stage_n1, n);
-        d2h(st, P->ahead_y.data(), (const double *)P->stage_m, m);
+        auto fetch = [&](std::vector<double> &to, const double *from, int64_t len) {
+            to.resize((size_t)len);
+            d2h(st, to.data(), from, len);
+        };
+        const int64_t n = P->noff[first + count] - P->noff[first], m = P->moff[first + count] - P->moff[first];
+        if (want & 1) fetch(P->ahead_x, P->stage_n0, n);
+        if (want & 2) fetch(P->ahead_y, P->stage_m, m);
+        if (want & 4) fetch(P->ahead_lam, P->stage_n1, n);
         bsync(P);
-        P->ahead_lo = i;
-        P->ahead_hi = i + count;
+        P->ahead_lo = first;
+        P->ahead_hi = first + count;
+        P->ahead_has |= want;
     }
     const int64_t n0 = P->noff[i] - P->noff[P->ahead_lo], m0 = P->moff[i] - P->moff[P->ahead_lo];
     if (x) std::copy_n(P->ahead_x.begin() + n0, P->n[i], x);
