@@ -209,13 +209,15 @@ int do_load(lp_shared *P, const lp_csr *K, const double *const *c, const double 
     // interleaved data; padded instances: zero data, bounds [0, 0]
     const int64_t N = n * Bp, M = m * Bp;
     std::vector<double> hc(N, 0.0), hl(N, 0.0), hu(N, 0.0), hq(M, 0.0);
+    const int W = 1 << P->lgW;
     for (int b = 0; b < B; ++b) {
+        const int64_t cn = P->at(n, 0, b), cm = P->at(m, 0, b);
         for (int64_t j = 0; j < n; ++j) {
-            hc[P->at(n, j, b)] = c[b][j];
-            hl[P->at(n, j, b)] = l[b][j];
-            hu[P->at(n, j, b)] = u[b][j];
+            hc[cn + j * W] = c[b][j];
+            hl[cn + j * W] = l[b][j];
+            hu[cn + j * W] = u[b][j];
         }
-        for (int64_t i = 0; i < m; ++i) hq[P->at(m, i, b)] = q[b][i];
+        for (int64_t i = 0; i < m; ++i) hq[cm + i * W] = q[b][i];
     }
     // unscaled norms per instance
     P->Nq.assign(Bp, 0.0);
@@ -258,10 +260,10 @@ int do_load(lp_shared *P, const lp_csr *K, const double *const *c, const double 
     if (P->opt.fixed_step) P->eta0 = P->opt.fixed_eta;
     // the factors replicated per instance, the scaled interleaved vectors
     std::vector<double> hDr(M), hDc(N);
-    for (int64_t i = 0; i < m; ++i)
-        for (int b = 0; b < Bp; ++b) hDr[P->at(m, i, b)] = P->Dr[i];
-    for (int64_t j = 0; j < n; ++j)
-        for (int b = 0; b < Bp; ++b) hDc[P->at(n, j, b)] = P->Dc[j];
+    for (int b = 0; b < Bp; b += W) {
+        for (int64_t i = 0; i < m; ++i) std::fill_n(&hDr[P->at(m, i, b)], W, P->Dr[i]);
+        for (int64_t j = 0; j < n; ++j) std::fill_n(&hDc[P->at(n, j, b)], W, P->Dc[j]);
+    }
     double *Drr = A.make<double>(M), *Dcr = A.make<double>(N);
     double *d_c = A.make<double>(N), *d_l = A.make<double>(N), *d_u = A.make<double>(N), *d_q = A.make<double>(M);
     double *cs = A.make<double>(N), *ls = A.make<double>(N), *us = A.make<double>(N), *qs = A.make<double>(M);
