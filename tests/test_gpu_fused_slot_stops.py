@@ -86,3 +86,25 @@ def test_resume_at_a_check(lpmod, precision, n, check_every, window):
     q.set_state(q.get_state())
     q.solve(1e-30, 5 * check_every)
     assert np.array_equal(p.get_state(), q.get_state())
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_time_limit_and_on(lpmod, oracle_mod, precision):
+    """The time limit's point is the one it reports on, and the saved state
+    goes on to an optimum."""
+    say(f"case fused time limit {precision}")
+    data = gen.tiny_lp(0)
+    o = oracle_mod.Oracle(data)
+    p = lpmod.Problem(data, precision=precision, persistent=0, window=7)
+    info = p.solve(1e-30, 10 ** 9, 0.05)
+    assert info["status"] == "TIME_LIMIT" and info["iterations"] > 0
+    x, y, _, _ = p.result()
+    ev = o.eval_unscaled(x, y)
+    # the reported quantities come from products kept through the averages: far
+    # from the optimum's last digits in either precision
+    assert info["pobj"] == pytest.approx(ev["pobj"], rel=1e-3 if precision == "mixed" else 1e-9)
+    p.set_state(p.get_state())
+    info = p.solve(1e-4, 200000)
+    assert info["status"] == "OPTIMAL"
+    x, y, _, _ = p.result()
+    assert o.eval_unscaled(x, y)["rel_kkt"] <= 1e-4 * (1 + 1e-6)
