@@ -149,8 +149,9 @@ typedef struct {
                                clearly fewer blocks).  0: one row per thread, in index order;
                                1: split by entries, each thread adding the products of 8 consecutive
                                entries row by row and a row that crosses those chunks finished from the
-                               chunks' open parts in a fixed order (a few long rows among short ones then
-                               no longer hold up their wavefront); -1 (default): split in a product of at
+                               chunks' open parts in a fixed order, with compensation in rows of more than
+                               64 entries (a few long rows among short ones then no longer hold up their
+                               wavefront); -1 (default): split in a product of at
                                least 1024 row blocks of 2048 (about 2 million nonzeros; in smaller ones the
                                split's extra barriers cost more than they save), and with autotune the
                                other form is timed on each product's chosen layout and kept when at
@@ -268,7 +269,11 @@ int lp_spmv_noalloc(lp_problem *P, int transpose, const double *in, double *out)
  * kernel_timing was set: which = 0 (K x' partial pass + fused dual step) or
  * 1 (K' y' partial pass + fused averages and next primal step); *count
  * launch pairs with *total_ms summed hipEvent time (the first window's only
- * with kernel_timing = 2).  Zeros when timing was off. */
+ * with kernel_timing = 2).  Where both products are one column slice without
+ * rows of more than 8192 entries each is one launch, and which = 1 holds the
+ * step decision too, which is a launch of its own and untimed otherwise.
+ * Timed slots launch the check kernels (untimed) every time, others only
+ * where a check can fall due.  Zeros when timing was off. */
 int lp_kernel_time(const lp_problem *P, int which, int64_t *count, double *total_ms);
 
 /* Measurement helper (not a step of the method): the rate of the random

@@ -13,9 +13,13 @@
 //               (Sec. 2, "Optimality termination criteria") and KKT_omega
 //               (Sec. 2, "Restart criteria") for the current and the averaged
 //               iterate, the restart decision, and the restart itself.
-// Decisions are taken on the device by single-workgroup kernels that write
-// the controller block (Ctl); every kernel reads it at its start, so the
-// host only polls a done flag once per window of attempts.
+// Products of one column slice without long rows run a slot in two kernels
+// instead (k_fused_dual, k_fused_update), the whole loop of a small LP runs in
+// one (k_small_loop and the forms after it).
+// Decisions are taken on the device: by single-workgroup kernels that write
+// the controller block (Ctl), the step's by every workgroup of k_fused_update
+// for itself; every kernel reads the controller at its start, so the host only
+// polls a done flag once per window of attempts.
 //
 // Each product is a column-sliced CSR-Stream pass (see Sliced in internal.h):
 // a workgroup stages the products v*x[col] of one row block in LDS with
@@ -23,9 +27,10 @@
 // or split by entries over the threads: Sliced::split); the slice of x it
 // gathers from stays resident in its XCD's L2.  The fused epilogue kernels
 // add the slices' partial rows in a fixed order.
-// Reductions are deterministic: each lane accumulates in FP64, wave64
-// butterflies and a fixed-order LDS step give one partial per workgroup, and
-// a single workgroup sums the partials in a fixed order.  No float atomics.
+// Reductions are deterministic: each lane accumulates in FP64, wave64 sums
+// (butterflies, or DPP moves in the short kernels) and a fixed-order LDS step
+// give one partial per workgroup, and the partials are summed in a fixed order.
+// No float atomics.
 #include "device.h"
 
 #include <algorithm>

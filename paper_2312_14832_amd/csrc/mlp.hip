@@ -14,8 +14,9 @@
 //     ascending steps of 16 whatever the tile, so the tile size changes no
 //     bit of a result: 256x256, 128x128 or 64x64 outputs per workgroup
 //     (k_gemm_mfma), picked by how well they fill the GPU (mfma_tile).
-//   FP32 mode: 64x64 tiles with FP32 FMA (every thread a 4x4 block); used to
-//     check gradients against the FP64 reference at FP32 accuracy.
+//   FP32 mode: 64x64 or 128x128 tiles with FP32 FMA (every thread 4x4 blocks,
+//     k_gemm_fp32); used to check gradients against the FP64 reference at FP32
+//     accuracy.
 // Long reductions (dL/dalpha contracts over out_dim) are split over
 // workgroups and the partial tiles are summed in a fixed order.
 #include <hip/hip_runtime.h>
@@ -200,10 +201,11 @@ void launch_fp32(const float *A, int lda, const float *B, int ldb, float *C, int
 // CU's four matrix cores, and the waves read their operands from LDS at 128
 // bytes a clock: with 64 x 64 to a wave (T = 128) that alone takes as long as
 // the MFMAs.  The 256 tile gives each of its eight waves 128 x 64: 4096^3 in
-// 146 us (944 TFLOP/s), where 128 x 128 tiles with scattered LDS writes took
-// 255; four waves of 128 x 128 spilled registers (200 us).  A small product
-// is a chain of stages instead: 256 x 1024 x 1024 went from 71 us (scalar
-// staging, one stage at a time) to 10.
+// 138 us, host call included (the kernel 127 to 143 us, 134 on average, 1.0
+// PFLOP/s), where 128 x 128 tiles with scattered LDS writes took 255; four waves
+// of 128 x 128 spilled registers (200 us).  A small product is a chain of stages
+// instead: the kernel of 256 x 1024 x 1024 went from 71 us (scalar staging, one
+// stage at a time) to 10.
 //
 // An operand is staged as it lies in memory, in 16-byte vectors with no
 // alignment asked of them (a global load takes any address; an odd leading
@@ -544,14 +546,16 @@ void launch_mfma(const GemmArgs &g, int splits, hipStream_t st)
 // very many columns: 256 x 300001 x 64 reads 38 MB and writes 307 MB, so it
 // is a stream of stores.  As tiles of a general product each workgroup spent
 // its life waiting for its one stage of K (157 us at best; 285 before, with
-// scalar loads and a bfloat16 copy of the output that nothing read).  Now
-// 137-150 us, and about 85 when the rows are whole cache lines (a multiple of
-// 32 columns): the partial lines at the rows' ends are what is left.  Here a
-// workgroup keeps its 256 rows of A in registers (64 rows to a
-// wave) and walks the column tiles, 64 wide (MSE: 32), with the next tile's weights on
-// their way while it stores this one's results.  Tiles go to XCDs in
-// contiguous runs: neighbours share the cache lines at their seam (rows of an
-// odd length are not aligned), which one L2 then completes.
+// scalar loads and a bfloat16 copy of the output that nothing read).  Now 124
+// us, and 82 at 300,032 columns, where every row is whole cache lines.  Of the
+// difference the output's partial lines are only a part: storing whole lines,
+// the results turned between lanes, took 112 (and 88 to 99 where rows are whole
+// lines anyway, so it was left out); the weights' rows are odd too.  Here a
+// workgroup keeps its 256 rows of A in registers (64 rows to a wave) and walks
+// the column tiles, 64 wide (MSE: 32), with the next tile's weights on their way
+// while it stores this one's results.  Tiles go to XCDs in contiguous runs:
+// neighbours share the cache lines at their seam (rows of an odd length are not
+// aligned), which one L2 then completes.
 //
 // MSE (a training step): the predictions z are not stored; of d = z - target
 // come dz = 2 d / (M N) as bfloat16 (Cb), the sum of d^2 over the workgroup's
