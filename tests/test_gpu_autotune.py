@@ -60,3 +60,19 @@ def test_tuned_handle(lpmod, oracle_mod, name, make, opt, precision):
     # the solve's products are those of lp_spmv, bit for bit
     assert np.array_equal(p.spmv(sg["x"]), sg["Kx"])
     assert np.array_equal(p.spmv(sg["y"], transpose=True), sg["KTy"])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("rows", [0, 5])
+def test_nothing_to_tune(lpmod, rows, precision):
+    """No rows, or rows without entries."""
+    say(f"case autotune without entries {rows} {precision}")
+    n = 40
+    data = gen.LPData(rows, n, 0, np.zeros(rows + 1, np.int32), np.zeros(0, np.int32), np.zeros(0),
+                      np.linspace(-1, 1, n), -np.ones(rows), np.zeros(n), np.full(n, 3.0))
+    for opt in (dict(), dict(persistent=0)):
+        p = lpmod.Problem(data, precision=precision, autotune=1, **opt)
+        info = p.solve(1e-6, 1000)
+        assert info["status"] == "OPTIMAL"
+        assert np.allclose(p.result()[0], np.where(data.c > 0, 0.0, 3.0), atol=1e-4)
+        assert np.array_equal(p.spmv(np.ones(n)), np.zeros(rows))
